@@ -18,17 +18,32 @@
 // weight's exponent E' + V'[n-k] - V'[n] is formed to the rounding of its
 // own size, not of V_B's.
 //
-//   k_boson_inner : inner-ring spring forces (sets f) and energies, one
-//                   thread per particle
-//   k_boson_seq   : one block: prefix sums, the forward recursion (V', the
-//                   ring weights w[n,k] into scratch, the weighted energy EV'
-//                   of the primitive estimator) and its adjoint (adj[n] =
-//                   dV'[N]/dV'[n]); sequential in n, parallel in k
-//   k_boson_rows  : one block per n: q[n,k] = adj[n] w[n,k] (the probability
-//                   of ring (n,k)'s closing link), and its suffix sums over k
-//   k_boson_links : one wave per particle: the chain links' probabilities
-//                   (sums of those suffix sums) and the link forces on the
-//                   particle's first and last beads
+// The recursion is a lower triangular linear system in Z[n] = exp(-beta_n V'[n]),
+//   Z[n] = (1/n) sum_j exp(-beta_n E'[n, n-j]) Z[j],   Z[0] = 1,
+// whose matrix is known up front.  With c[m] the chain links' prefix sums and
+// Y[n] = exp(beta_n c[n]) Z[n] its entries need one link each,
+//   Y[n] = (1/n) exp(beta_n L[n-1,n]) sum_j exp(-beta_n L[n-1,j]) Y[j],
+// so the whole chip forms them first and one block then solves the system by
+// blocks of 64: multiply-adds along the serial chain, no exponential, no
+// logarithm and no reduction across lanes.  Y spans thousands of binary
+// orders, so entries and Y are (mantissa, exponent) pairs.
+//
+//   k_boson_prep  : inner-ring spring forces (sets f) and energies; the
+//                   system's matrix in tiles; the chain links' prefix sums
+//   k_boson_solve : one block: Y and V'[N]
+//   k_boson_weights: a block per tile: the ring weights w[n,k] and the rows'
+//                   weighted ring energies
+//   k_boson_adjoint: one block: adj[n] = dV'[N]/dV'[n] by blocks of 64 from
+//                   the end; V_B and EV_B
+//   k_boson_rows  : a wave per n: q[n,k] = adj[n] w[n,k] (the probability of
+//                   ring (n,k)'s closing link), its running sums over the
+//                   columns, and the closing links' forces on the last bead
+//   k_boson_cols  : 16 lanes per particle group: the chain links'
+//                   probabilities (column sums of those running sums) and
+//                   the remaining link forces
+// Links beyond kWideLink (in units of 1/beta_n), where the exponents would
+// leave 32 bits, and non-finite ones send the call through the recursion in
+// log space (seq_recursion: one block of k_boson_weights, sequential in n).
 #include "../../include/pimd.h"
 #include "pimd_internal.h"
 #include "pimd_device.h"
@@ -47,10 +62,67 @@ static __device__ __align__(256) double scratch[boson_scr_doubles(kBosonNoAllocM
 
 namespace {
 
-constexpr int kSeq = 256;   // threads of the sequential kernel
+constexpr int kSeq = 256;   // threads of the recursion in log space
 constexpr int kSeqU = (kBosonMaxN + kSeq - 1) / kSeq;   // k per thread and stage
+constexpr int kSolve = 1024;   // threads of the blocked solves
+constexpr int kSolveWaves = kSolve / 64;
+constexpr int kT = kBosonTile;
+constexpr int kTT = kT * kT;
 
-__device__ __forceinline__ size_t tri_row(int n) { return (size_t)n * (size_t)(n - 1) / 2; }
+// beta_n times a link's energy, at most, in the blocked solve: exponents up to
+// 2^18 per factor stay below 2^29 through 1024 particles' products
+constexpr double kWideLink = 131072.0;
+constexpr int kNoExp = -(1 << 30);   // exponent of an exact zero
+
+// Scratch (see pimd_internal.h)
+struct BosonScr {
+    double *w;      // [tiles][64 rows n][64 columns j] ring weights; first
+                    // [tiles][64 columns][64 rows] mantissas of the matrix
+    double *s;      // [tiles][64][64] running probabilities over j
+    int *ge;        // [tiles][64 columns][64 rows] exponents (in s's place)
+    double *ym;     // [N+1] Y: mantissa in [0.5, 1), exponent
+    int *ye;
+    double *xm;     // [N+1] exp(beta_n L[n-1,n]) (1 for n = N), likewise
+    int *xe;
+    double *chi, *clo;   // [N+1] prefix sums of the chain links (double-double)
+    double *adj;    // [N+1]
+    double *e0, *el;     // [N][3] the particles' first and last beads
+    double *eb;     // [tiles][64] the tiles' shares of sum_k w[n,k] E'[n,k]
+    double *ein;    // [kBosonInnerMax] inner spring energies per block
+    double *vp;     // [2] V'[N] (double-double)
+    int *wide;      // [tiles] 1: a link of the tile is beyond kWideLink
+    int *slow;      // [1] 1: this call went through seq_recursion
+
+    __device__ explicit BosonScr(const BosonArgs &a)
+    {
+        const int N = a.N;
+        const size_t tri = boson_scr_tri(N), n1 = (size_t)N + 1;
+        w = a.scr;
+        s = w + tri;
+        ge = reinterpret_cast<int *>(s);
+        ym = s + tri;
+        ye = reinterpret_cast<int *>(ym + n1);
+        xm = ym + 2 * n1;
+        xe = reinterpret_cast<int *>(ym + 3 * n1);
+        chi = ym + 4 * n1;
+        clo = ym + 5 * n1;
+        adj = ym + 6 * n1;
+        e0 = ym + 7 * n1;
+        el = ym + 10 * n1;
+        eb = ym + 13 * n1;
+        ein = eb + (size_t)boson_tiles(N) * kT;
+        vp = ein + kBosonInnerMax;
+        wide = reinterpret_cast<int *>(vp + 2);
+        slow = reinterpret_cast<int *>(vp + 2 + boson_tiles(N));
+    }
+};
+
+// place of w[n, n-j] in the tiles
+__device__ __forceinline__ size_t w_at(int n, int j)
+{
+    const int b = (n - 1) / kT, r = (n - 1) - b * kT, cb = j / kT;
+    return ((size_t)boson_tile(b, cb) * kT + r) * kT + (j - cb * kT);
+}
 
 __device__ __forceinline__ size_t bidx(const BosonArgs &a, int j, int l, int d)
 {
@@ -149,35 +221,6 @@ __device__ __forceinline__ void seq_sum2(double &a, double &b, double *red)
     b = rb;
 }
 
-// Inner-ring springs: forces on every bead (overwrites f) and each particle's
-// inner spring energy eint[l] = kspring sum_j |x_{j+1} - x_j|^2.
-__global__ __launch_bounds__(kBlock) void k_boson_inner(BosonArgs a)
-{
-    const int l = blockIdx.x * kBlock + threadIdx.x;
-    if (l >= a.N) return;
-    const int P = a.P;
-    const double k2 = 2.0 * a.ks;
-    double e = 0.0;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        double prev = 0.0, cur = a.x[bidx(a, 0, l, d)];
-        for (int j = 0; j < P; ++j) {
-            const double next = (j + 1 < P) ? a.x[bidx(a, j + 1, l, d)] : 0.0;
-            double g = 0.0;
-            if (j + 1 < P) {
-                const double u = next - cur;
-                g += k2 * u;
-                e += u * u;
-            }
-            if (j > 0) g -= k2 * (cur - prev);
-            a.f[bidx(a, j, l, d)] = g;
-            prev = cur;
-            cur = next;
-        }
-    }
-    a.scr[boson_scr_eint(a.N) + l] = a.ks * e;
-}
-
 struct SeqLds {
     double e0[kBosonMaxN * 3];      // bead 0 of each particle
     double el[kBosonMaxN * 3];      // bead P-1
@@ -186,9 +229,22 @@ struct SeqLds {
     double vhi[kBosonMaxN + 1];     // V' (double-double)
     double vlo[kBosonMaxN + 1];
     double ev[kBosonMaxN + 1];      // EV'
-    double adj[kBosonMaxN + 1];     // dV'[N]/dV'[n]; first the scan of chunk totals
+    double adj[kBosonMaxN + 1];     // dV'[N]/dV'[n]
     double red[16];
 };
+
+// Blocks of the inner springs (four bead coordinates per thread).
+__host__ __device__ inline int inner_blocks(int N, int P)
+{
+    const int nb = (int)(((long long)N * 3 * P + 4 * kBlock - 1) / (4 * kBlock));
+    return nb < kBosonInnerMax ? nb : kBosonInnerMax;
+}
+
+// this thread's share of the inner spring energies' sum
+__device__ __forceinline__ double inner_sum(const BosonArgs &a, const BosonScr &scr, int t)
+{
+    return t < inner_blocks(a.N, a.P) ? scr.ein[t] : 0.0;
+}
 
 __device__ __forceinline__ double link_e(const SeqLds &s, const BosonArgs &a, int l, int l2)
 {
@@ -201,56 +257,27 @@ __device__ __forceinline__ double link_e(const SeqLds &s, const BosonArgs &a, in
     return a.ks * e;
 }
 
-__global__ __launch_bounds__(kSeq) void k_boson_seq(BosonArgs a)
+// The recursion in log space, sequential in n, parallel in k: V', the ring
+// weights, EV' and the adjoints, for the calls that the blocked solve does not
+// take.  One block.
+__device__ __forceinline__ void seq_recursion(const BosonArgs &a, SeqLds &s)
 {
-    __shared__ SeqLds s;
     const int t = threadIdx.x, N = a.N;
-    double *w = a.scr;                               // ring weights w[n,k]
+    const BosonScr scr(a);
+    double *w = scr.w;                               // ring weights w[n,k]
     for (int e = t; e < N * 3; e += kSeq) {
-        const int l = e / 3, d = e - l * 3;
-        s.e0[e] = a.x[bidx(a, 0, l, d)];
-        s.el[e] = a.x[bidx(a, a.P - 1, l, d)];
+        s.e0[e] = scr.e0[e];
+        s.el[e] = scr.el[e];
+    }
+    for (int m = t; m < N; m += kSeq) {
+        s.chi[m] = scr.chi[m];
+        s.clo[m] = scr.clo[m];
     }
     // the inner energies' sum, thread-strided, then in wave order
-    double esum = 0.0;
-    for (int l = t; l < N; l += kSeq) esum += a.scr[boson_scr_eint(N) + l];
+    double esum = inner_sum(a, scr, t);
     {
         double dummy = 0.0;
         seq_sum2(esum, dummy, s.red);   // (its barrier also publishes e0, el)
-    }
-    // Prefix sums ch[m] = sum_{l<m} link(l, l+1), m = 0..N-1, in
-    // double-double: each thread sums a contiguous chunk, the chunk totals
-    // are scanned (Hillis-Steele), then each chunk is written out.
-    const int nl = N - 1;                            // chain links
-    const int C = (nl + kSeq - 1) / kSeq;
-    const int l0 = t * C, l1 = min(l0 + C, nl);
-    DD tot = {0.0, 0.0};
-    for (int l = l0; l < l1; ++l) tot = dd_add1(tot, link_e(s, a, l, l + 1));
-    s.adj[t] = tot.hi;
-    s.ev[t] = tot.lo;
-    __syncthreads();
-    for (int off = 1; off < kSeq; off <<= 1) {
-        DD add = {0.0, 0.0};
-        if (t >= off) add = {s.adj[t - off], s.ev[t - off]};
-        __syncthreads();
-        if (t >= off) {
-            const DD v = dd_add({s.adj[t], s.ev[t]}, add);
-            s.adj[t] = v.hi;
-            s.ev[t] = v.lo;
-        }
-        __syncthreads();
-    }
-    DD run = {0.0, 0.0};
-    if (t > 0) run = {s.adj[t - 1], s.ev[t - 1]};
-    __syncthreads();   // the scan's slots are read before s.ev is reused
-    if (t == 0) {
-        s.chi[0] = 0.0;
-        s.clo[0] = 0.0;
-    }
-    for (int l = l0; l < l1; ++l) {
-        run = dd_add1(run, link_e(s, a, l, l + 1));
-        s.chi[l + 1] = run.hi;
-        s.clo[l + 1] = run.lo;
     }
     if (t == 0) {
         s.vhi[0] = 0.0;
@@ -304,7 +331,7 @@ __global__ __launch_bounds__(kSeq) void k_boson_seq(BosonArgs a)
 #pragma unroll
         for (int u = 0; u < kSeqU; ++u) {
             const int k = 1 + t + u * kSeq;
-            if (k <= n) w[tri_row(n) + (k - 1)] = ex[u] * isw;
+            if (k <= n) w[w_at(n, n - k)] = ex[u] * isw;
         }
         if (t == 0) {
             s.vhi[n] = vprev.hi;
@@ -320,7 +347,7 @@ __global__ __launch_bounds__(kSeq) void k_boson_seq(BosonArgs a)
 #pragma unroll
         for (int u = 0; u < kSeqU; ++u) {
             const int k = 1 + t + u * kSeq;
-            wr[u] = (k <= n) ? w[tri_row(n) + (k - 1)] : 0.0;
+            wr[u] = (k <= n) ? w[w_at(n, n - k)] : 0.0;
         }
         __syncthreads();
         const double an = s.adj[n];
@@ -331,7 +358,7 @@ __global__ __launch_bounds__(kSeq) void k_boson_seq(BosonArgs a)
         }
     }
     __syncthreads();
-    for (int e = t; e <= N; e += kSeq) a.scr[boson_scr_adj(N) + e] = s.adj[e];
+    for (int e = t; e <= N; e += kSeq) scr.adj[e] = s.adj[e];
     if (t == 0) {
         const DD vb = dd_add1({s.vhi[N], s.vlo[N]}, esum);
         a.res[0] = vb.hi + vb.lo;
@@ -339,124 +366,684 @@ __global__ __launch_bounds__(kSeq) void k_boson_seq(BosonArgs a)
     }
 }
 
-// Row n = blockIdx.x + 1: q[n,k] = adj[n] w[n,k], the probability of ring
-// (n,k)'s closing link n-1 -> n-k; T[n,k] = sum_{k' >= k} q[n,k'] (each
-// thread a contiguous chunk of k, then a scan of the chunk totals from the
-// right).  With prob, row n-1 of it gets the closing links and zeros (its
-// chain entry n is written by k_boson_links).
-__global__ __launch_bounds__(kBlock) void k_boson_rows(BosonArgs a)
+// --- the blocked solve -------------------------------------------------------
+// (mantissa, exponent) += (tm, te); mantissas are >= 0, and exact zeros carry
+// kNoExp.  The sum keeps the larger exponent, unnormalized: within a block of
+// 64 additions and products mantissas stay within 2^(+-500).
+__device__ __forceinline__ void ext_add(double &am, int &ae, double tm, int te)
 {
-    __shared__ double tot[kBlock];
-    const int n = blockIdx.x + 1, t = threadIdx.x, N = a.N;
-    const double an = a.scr[boson_scr_adj(N) + n];
-    const double *w = a.scr + tri_row(n);
-    double *T = a.scr + boson_scr_tri(N) + tri_row(n);
+    const int e = max(ae, te);
+    am = ldexp(am, ae - e) + ldexp(tm, te - e);
+    ae = e;
+}
+
+// exp(p + plo) = m 2^k, m in about [0.7, 1.42), for |p| <= kWideLink: p - k ln 2
+// exactly through ln 2's high part (k ln 2_hi has at most 59 bits, the
+// difference at most 53), then the Taylor series to r^13 (|r| <= 0.347, next
+// term below 2^-57).
+__device__ __forceinline__ void exp_ext(double p, double plo, double &m, int &k)
+{
+    const double LN2_HI = 0x1.62e42fefa2p-1, LN2_LO = 0x1.9ef35793c7673p-41;
+    const double kd = rint(p * 1.4426950408889634074);
+    double r = fma(-kd, LN2_HI, p);
+    r += fma(-kd, LN2_LO, plo);
+    double q = 1.0 / 6227020800.0;
+    q = fma(q, r, 1.0 / 479001600.0);
+    q = fma(q, r, 1.0 / 39916800.0);
+    q = fma(q, r, 1.0 / 3628800.0);
+    q = fma(q, r, 1.0 / 362880.0);
+    q = fma(q, r, 1.0 / 40320.0);
+    q = fma(q, r, 1.0 / 5040.0);
+    q = fma(q, r, 1.0 / 720.0);
+    q = fma(q, r, 1.0 / 120.0);
+    q = fma(q, r, 1.0 / 24.0);
+    q = fma(q, r, 1.0 / 6.0);
+    q = fma(q, r, 0.5);
+    m = fma(r * r, q, r) + 1.0;
+    k = (int)kd;
+}
+
+__device__ __forceinline__ double link3(const BosonArgs &a, const double *el, const double *e0)
+{
+    double e = 0.0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double u = mic(e0[d], el[d], a.box[d]);
+        e += u * u;
+    }
+    return a.ks * e;
+}
+
+// Blocks 0..tiles-1: the matrix exp(beta_n (L[n-1,n] - L[n-1,j])) / n, one
+// 64 x 64 tile each (column by column, a row per lane: the order in which the
+// solve reads it).  Then the inner springs (forces on every bead, overwriting
+// f, elementwise so that either layout is read in order; one partial energy per
+// block).  The last block: the particles' end beads, packed, and the chain
+// links' prefix sums.  N = 1024, P = 32: 7 us (the inner springs alone took
+// 38 us with a thread per particle, whose reads are a bead row apart).
+__global__ __launch_bounds__(kBlock) void k_boson_prep(BosonArgs a)
+{
+    __shared__ double sh[2 * kBlock];
+    const int t = threadIdx.x, N = a.N, P = a.P;
+    const BosonScr scr(a);
+    const int tiles = boson_tiles(N), inner = inner_blocks(N, P);
+    if ((int)blockIdx.x < tiles) {
+        const int tile = blockIdx.x;
+        int b = (int)((sqrtf(8.0f * (float)tile + 1.0f) - 1.0f) * 0.5f);
+        while (boson_tile(b + 1, 0) <= tile) ++b;
+        while (boson_tile(b, 0) > tile) --b;
+        const int cb = tile - boson_tile(b, 0);
+        const int r = t & 63, n = b * kT + 1 + r;
+        if (t < 3 * kT) {
+            const int j = cb * kT + t / 3;
+            sh[t] = j < N ? a.x[bidx(a, 0, j, t % 3)] : 0.0;
+        }
+        // the row's particle n-1: its last bead, and the chain link to n
+        double el[3] = {0.0, 0.0, 0.0}, xm = 1.0;
+        int xe = 0;
+        bool bad = false;
+        if (n <= N) {
+            double e0n[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                el[d] = a.x[bidx(a, P - 1, n - 1, d)];
+                if (n < N) e0n[d] = a.x[bidx(a, 0, n, d)];
+            }
+            if (n < N) {
+                const double L = link3(a, el, e0n), p = a.bn * L;
+                bad = !(p <= kWideLink);
+                if (!bad) exp_ext(p, fma(a.bn, L, -p), xm, xe);
+            }
+            if (cb == b && t < kT) {
+                scr.xm[n] = xm;
+                scr.xe[n] = xe;
+            }
+        }
+        const double hm = xm / (double)n;
+        __syncthreads();
+        double *gm = scr.w + (size_t)tile * kTT;
+        int *ge = scr.ge + (size_t)tile * kTT;
+        for (int c = t >> 6; c < kT; c += kBlock / 64) {
+            const int j = cb * kT + c;
+            double m = 0.0;
+            int e = kNoExp;
+            if (n <= N && j < n) {
+                const double L = link3(a, el, sh + 3 * c), p = a.bn * L;
+                if (p <= kWideLink) {
+                    int k;
+                    exp_ext(-p, -fma(a.bn, L, -p), m, k);
+                    m *= hm;
+                    e = k + xe + __builtin_amdgcn_frexp_exp(m);
+                    m = __builtin_amdgcn_frexp_mant(m);
+                } else {
+                    bad = true;
+                }
+            }
+            gm[c * kT + r] = m;
+            ge[c * kT + r] = e;
+        }
+        const int any = __syncthreads_or(bad ? 1 : 0);
+        if (t == 0) scr.wide[tile] = any;
+        return;
+    }
+    if ((int)blockIdx.x < tiles + inner) {
+        const int ib = blockIdx.x - tiles;
+        const size_t n3p = (size_t)N * 3 * P, stride = a.layout ? 1 : (size_t)N * 3;
+        const double k2 = 2.0 * a.ks;
+        double e2 = 0.0;
+        for (size_t e = (size_t)ib * kBlock + t; e < n3p; e += (size_t)inner * kBlock) {
+            const int j = a.layout ? (int)(e % P) : (int)(e / stride);
+            const double cur = a.x[e];
+            const double next = j + 1 < P ? a.x[e + stride] : 0.0;
+            const double prev = j > 0 ? a.x[e - stride] : 0.0;
+            double g = 0.0;
+            if (j + 1 < P) {
+                const double u = next - cur;
+                g += k2 * u;
+                e2 += u * u;
+            }
+            if (j > 0) g -= k2 * (cur - prev);
+            a.f[e] = g;
+        }
+        double s1[1] = {e2};
+        block_sum<1>(s1, sh);
+        if (t == 0) scr.ein[ib] = a.ks * s1[0];
+        return;
+    }
+    // end beads, and the prefix sums ch[m] = sum_{l<m} link(l, l+1), m = 0..N-1,
+    // in double-double: each thread sums a contiguous chunk, the chunk totals
+    // are scanned (Hillis-Steele), then each chunk is written out
+    for (int e = t; e < N * 3; e += kBlock) {
+        const int l = e / 3, d = e - l * 3;
+        scr.e0[e] = a.x[bidx(a, 0, l, d)];
+        scr.el[e] = a.x[bidx(a, P - 1, l, d)];
+    }
     constexpr int CU = (kBosonMaxN + kBlock - 1) / kBlock;
-    const int C = (n + kBlock - 1) / kBlock;
-    const int k0 = 1 + t * C;
-    double q[CU];
-    double acc = 0.0;
+    const int nl = N - 1;                            // chain links
+    const int C = (nl + kBlock - 1) / kBlock;
+    const int l0 = t * C;
+    double L[CU];
+    DD tot = {0.0, 0.0};
 #pragma unroll
-    for (int u = CU - 1; u >= 0; --u) {
-        const int k = k0 + u;
-        q[u] = 0.0;
-        if (u < C && k <= n) {
-            q[u] = an * w[k - 1];
-            acc += q[u];
+    for (int u = 0; u < CU; ++u) {
+        const int l = l0 + u;
+        L[u] = 0.0;
+        if (u < C && l < nl) {
+            double el[3], e0[3];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                el[d] = a.x[bidx(a, P - 1, l, d)];
+                e0[d] = a.x[bidx(a, 0, l + 1, d)];
+            }
+            L[u] = link3(a, el, e0);
+            tot = dd_add1(tot, L[u]);
         }
     }
-    tot[t] = acc;
+    double *hi = sh, *lo = sh + kBlock;
+    hi[t] = tot.hi;
+    lo[t] = tot.lo;
     __syncthreads();
-    // suffix scan of the chunk totals: tot[t] = sum over threads >= t
     for (int off = 1; off < kBlock; off <<= 1) {
-        const double add = (t + off < kBlock) ? tot[t + off] : 0.0;
+        DD add = {0.0, 0.0};
+        if (t >= off) add = {hi[t - off], lo[t - off]};
         __syncthreads();
-        tot[t] += add;
+        if (t >= off) {
+            const DD v = dd_add({hi[t], lo[t]}, add);
+            hi[t] = v.hi;
+            lo[t] = v.lo;
+        }
         __syncthreads();
     }
-    double run = (t + 1 < kBlock) ? tot[t + 1] : 0.0;
-#pragma unroll
-    for (int u = CU - 1; u >= 0; --u) {
-        const int k = k0 + u;
-        if (u < C && k <= n) {
-            run += q[u];
-            T[k - 1] = run;
-        }
+    DD run = {0.0, 0.0};
+    if (t > 0) run = {hi[t - 1], lo[t - 1]};
+    if (t == 0) {
+        scr.chi[0] = 0.0;
+        scr.clo[0] = 0.0;
     }
-    if (a.prob) {
-        double *row = a.prob + (size_t)(n - 1) * N;
 #pragma unroll
-        for (int u = 0; u < CU; ++u) {
-            const int k = k0 + u;
-            if (u < C && k <= n) row[n - k] = q[u];
+    for (int u = 0; u < CU; ++u) {
+        const int l = l0 + u;
+        if (u < C && l < nl) {
+            run = dd_add1(run, L[u]);
+            scr.chi[l + 1] = run.hi;
+            scr.clo[l + 1] = run.lo;
         }
-        for (int j = n + t; j < N; j += kBlock) row[j] = 0.0;
     }
 }
 
-// One wave per particle l: the chain links' probabilities
-//   chain[l] = sum_{n=l+2..N} T[n, n-l]   (the rings in which l -> l+1 is a link)
-// and the link forces on its last bead (links l -> l', l' <= l+1) and its
-// first bead (links l'' -> l, l'' >= l-1).
-__global__ __launch_bounds__(kBlock) void k_boson_links(BosonArgs a)
+__device__ __forceinline__ double lane_of(double v, int lane)
 {
-    const int lane = threadIdx.x & 63;
-    const int l = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-    const int N = a.N;
-    if (l >= N) return;
-    const double *w = a.scr;
-    const double *T = a.scr + boson_scr_tri(N);
-    const double *adj = a.scr + boson_scr_adj(N);
-    auto X = [&](int j, int p, int d) { return a.x[bidx(a, j, p, d)]; };
-    double cl = 0.0, cm = 0.0;
-    for (int n = l + 2 + lane; n <= N; n += 64) cl += T[tri_row(n) + (n - l) - 1];
-    if (l >= 1)
-        for (int n = l + 1 + lane; n <= N; n += 64) cm += T[tri_row(n) + (n - l + 1) - 1];
-    cl = wave_sum(cl);
-    cm = wave_sum(cm);
-    const double k2 = 2.0 * a.ks;
-    const int Pl = a.P - 1;
-    double el[3], e0[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        el[d] = X(Pl, l, d);
-        e0[d] = X(0, l, d);
+    union { double d; int i[2]; } u;
+    u.d = v;
+    u.i[0] = __builtin_amdgcn_readlane(u.i[0], lane);
+    u.i[1] = __builtin_amdgcn_readlane(u.i[1], lane);
+    return u.d;
+}
+
+struct SolveLds {
+    double gm[2][kTT];              // the current and the next diagonal tile
+    int ge[2][kTT];
+    double ym[kBosonMaxN + 1];      // Y
+    int ye[kBosonMaxN + 1];
+    double pm[kSolveWaves][kT];       // the waves' sums over the columns before the block
+    int pe[kSolveWaves][kT];
+};
+
+// The triangular system, one block, by blocks of 64 rows.  Wave 0 solves the
+// diagonal tile: lane r holds row r's sum, and step c broadcasts the Y that
+// lane c-1 has just finished, so a step is one broadcast and one multiply-add
+// of (mantissa, exponent) deep.  Meanwhile waves 1..15 sum the next block's
+// rows over the columns known so far, and once the tile is solved they add its
+// 64 columns, fetched ahead.  Bound by the diagonal tiles' chain (64 steps)
+// and, at large N, by one CU's reads of the matrix (12 B per entry).
+__global__ __launch_bounds__(kSolve) void k_boson_solve(BosonArgs a)
+{
+    __shared__ SolveLds s;
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63, N = a.N;
+    const BosonScr scr(a);
+    const int nb = boson_blocks(N), tiles = boson_tiles(N);
+    const int slow = __syncthreads_or(t < tiles ? scr.wide[t] : 0);
+    static_assert(boson_tiles(kBosonMaxN) <= kSolve, "one flag per thread");
+    if (t == 0) scr.slow[0] = slow ? 1 : 0;
+    if (slow) return;                            // k_boson_weights runs seq_recursion
+    constexpr int W = kSolveWaves - 1;             // waves that sum ahead
+    constexpr int NB = (kT + W - 1) / W;         // columns of the last block per such wave
+    double am = 0.0;
+    int ae = kNoExp;
+    for (int e = t; e < kTT; e += kSolve) {
+        s.gm[0][e] = scr.w[e];
+        s.ge[0][e] = scr.ge[e];
     }
-    // last bead: closing links l -> l' (ring (l+1, l+1-l')), then the chain
-    double g[3] = {0.0, 0.0, 0.0};
-    const double an = adj[l + 1];
-    for (int lp = lane; lp <= l; lp += 64) {
-        const double q = an * w[tri_row(l + 1) + (l - lp)];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) g[d] += k2 * q * mic(X(0, lp, d), el[d], a.box[d]);
+    if (t == 0) {
+        s.ym[0] = 0.5;
+        s.ye[0] = 1;
+        scr.ym[0] = 0.5;
+        scr.ye[0] = 1;
     }
-    // first bead: closing links m -> l (ring (m+1, m+1-l)), m = l..N-1
-    double h[3] = {0.0, 0.0, 0.0};
-    for (int m = l + lane; m < N; m += 64) {
-        const double q = adj[m + 1] * w[tri_row(m + 1) + (m - l)];
+    __syncthreads();
+    for (int b = 0; b < nb; ++b) {
+        double bm[NB];
+        int be[NB];
+        if (w == 0) {
+            __builtin_amdgcn_s_setprio(3);
+            const double *gm = s.gm[b & 1];
+            const int *ge = s.ge[b & 1];
+            ext_add(am, ae, gm[lane] * s.ym[b * kT], ge[lane] + s.ye[b * kT]);
+#pragma unroll 9
+            for (int c = 1; c < kT; ++c) {
+                const double ym = lane_of(am, c - 1);
+                const int ye = __builtin_amdgcn_readlane(ae, c - 1);
+                ext_add(am, ae, gm[c * kT + lane] * ym, ge[c * kT + lane] + ye);
+            }
+            __builtin_amdgcn_s_setprio(0);
+            const int n = b * kT + 1 + lane;
+            if (n <= N) {
+                const double m = __builtin_amdgcn_frexp_mant(am);
+                const int e = ae + __builtin_amdgcn_frexp_exp(am);
+                s.ym[n] = m;
+                s.ye[n] = e;
+                scr.ym[n] = m;
+                scr.ye[n] = e;
+            }
+        } else if (b + 1 < nb) {
+            const size_t row = (size_t)boson_tile(b + 1, 0) * kTT + lane;
+            const size_t dg = (size_t)boson_tile(b + 1, b + 1) * kTT;
+            for (int e = t - 64; e < kTT; e += 64 * W) {
+                s.gm[(b + 1) & 1][e] = scr.w[dg + e];
+                s.ge[(b + 1) & 1][e] = scr.ge[dg + e];
+            }
+            am = 0.0;
+            ae = kNoExp;
+            constexpr int U = 8;
+            for (int j0 = w - 1; j0 < b * kT; j0 += W * U) {
+                double g[U];
+                int e[U];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) h[d] -= k2 * q * mic(e0[d], X(Pl, m, d), a.box[d]);
+                for (int u = 0; u < U; ++u) {
+                    const int j = j0 + u * W;
+                    const bool in = j < b * kT;
+                    g[u] = in ? scr.w[row + (size_t)j * kT] : 0.0;
+                    e[u] = in ? scr.ge[row + (size_t)j * kT] : kNoExp;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int j = min(j0 + u * W, b * kT - 1);
+                    ext_add(am, ae, g[u] * s.ym[j], e[u] + s.ye[j]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int c = w - 1 + u * W;
+                bm[u] = c < kT ? scr.w[row + (size_t)(b * kT + c) * kT] : 0.0;
+                be[u] = c < kT ? scr.ge[row + (size_t)(b * kT + c) * kT] : kNoExp;
+            }
+        }
+        __syncthreads();
+        if (b + 1 == nb) break;
+        if (w > 0) {
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int j = b * kT + min(w - 1 + u * W, kT - 1);
+                ext_add(am, ae, bm[u] * s.ym[j], be[u] + s.ye[j]);
+            }
+            s.pm[w][lane] = am;
+            s.pe[w][lane] = ae;
+        }
+        __syncthreads();
+        if (w == 0) {
+            int e = kNoExp;
+#pragma unroll
+            for (int u = 1; u <= W; ++u) e = max(e, s.pe[u][lane]);
+            am = 0.0;
+#pragma unroll
+            for (int u = 1; u <= W; ++u) am += ldexp(s.pm[u][lane], s.pe[u][lane] - e);
+            ae = e;
+        }
+    }
+    // V'[N] = -(1/beta_n) sum_n ln(Z[n]/Z[n-1]), Z[n]/Z[n-1] = Y[n] /
+    // (exp(beta_n L[n-1,n]) Y[n-1]): each term of V'[n] - V'[n-1]'s own size,
+    // summed in double-double
+    DD v = {0.0, 0.0};
+    if (t < N) {
+        const int n = t + 1;
+        const double LN2_HI = 0x1.62e42fefa2p-1, LN2_LO = 0x1.9ef35793c7673p-41;
+        const double m = s.ym[n] / (scr.xm[n] * s.ym[n - 1]);
+        const double e = (double)(s.ye[n] - scr.xe[n] - s.ye[n - 1]);
+        v.hi = -fma(e, LN2_HI, fma(e, LN2_LO, log(m))) / a.bn;
     }
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        g[d] = wave_sum(g[d]);
-        h[d] = wave_sum(h[d]);
-    }
+    for (int o = 32; o > 0; o >>= 1) v = dd_add(v, {__shfl_xor(v.hi, o), __shfl_xor(v.lo, o)});
     if (lane == 0) {
-        if (l + 1 < N) {
+        s.pm[w][0] = v.hi;
+        s.pm[w][1] = v.lo;
+    }
+    __syncthreads();
+    if (t == 0) {
+        for (int u = 1; u < kSolveWaves; ++u) v = dd_add(v, {s.pm[u][0], s.pm[u][1]});
+        scr.vp[0] = v.hi;
+        scr.vp[1] = v.lo;
+    }
+}
+
+struct WeightLds {
+    double w[kT * (kT + 1)];
+    double e0[3 * kT];              // the columns' first beads, Y and chain sums
+    double ym[kT];
+    double ch[2 * kT];
+    int ye[kT];
+};
+
+// Ring weights of one tile, w[n,k] = G[n,j] Y[j] / Y[n] (j = n - k), written
+// row by row (the order in which the adjoint and the links read them), and the
+// tile's share of each row's sum_k w[n,k] E'[n,k].  A call that the solve left
+// runs the recursion in log space here instead (block 0).
+__global__ __launch_bounds__(kBlock) void k_boson_weights(BosonArgs a)
+{
+    __shared__ union { WeightLds v; SeqLds q; } lds;
+    double *sW = lds.v.w, *sE = lds.v.e0, *sYm = lds.v.ym, *sC = lds.v.ch;
+    int *sYe = lds.v.ye;
+    const int t = threadIdx.x, N = a.N, tile = blockIdx.x;
+    const BosonScr scr(a);
+    if (scr.slow[0]) {
+        if (tile == 0) seq_recursion(a, lds.q);
+        return;
+    }
+    int b = (int)((sqrtf(8.0f * (float)tile + 1.0f) - 1.0f) * 0.5f);
+    while (boson_tile(b + 1, 0) <= tile) ++b;
+    while (boson_tile(b, 0) > tile) --b;
+    const int cb = tile - boson_tile(b, 0);
+    const int r = t & 63, n = b * kT + 1 + r;
+    double *wt = scr.w + (size_t)tile * kTT;
+    const int *ge = scr.ge + (size_t)tile * kTT;
+    constexpr int NC = kT / (kBlock / 64);
+    double g[NC];
+    int e[NC];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) g[d] += k2 * cl * mic(X(0, l + 1, d), el[d], a.box[d]);
-            if (a.prob) a.prob[(size_t)l * N + l + 1] = cl;
-        }
-        if (l >= 1) {
+    for (int u = 0; u < NC; ++u) {
+        const int c = (t >> 6) + u * (kBlock / 64);
+        g[u] = wt[c * kT + r];
+        e[u] = ge[c * kT + r];
+    }
+    if (t < 3 * kT) sE[t] = cb * kT + t / 3 < N ? scr.e0[cb * kT * 3 + t] : 0.0;
+    if (t < kT && cb * kT + t < N) {
+        sYm[t] = scr.ym[cb * kT + t];
+        sYe[t] = scr.ye[cb * kT + t];
+        sC[t] = scr.chi[cb * kT + t];
+        sC[kT + t] = scr.clo[cb * kT + t];
+    }
+    double el[3] = {0.0, 0.0, 0.0}, iy = 0.0;
+    DD cn = {0.0, 0.0};
+    int yn = 0;
+    if (n <= N) {
 #pragma unroll
-            for (int d = 0; d < 3; ++d) h[d] -= k2 * cm * mic(e0[d], X(Pl, l - 1, d), a.box[d]);
+        for (int d = 0; d < 3; ++d) el[d] = scr.el[(n - 1) * 3 + d];
+        iy = 1.0 / scr.ym[n];
+        yn = scr.ye[n];
+        cn = {scr.chi[n - 1], scr.clo[n - 1]};
+    }
+    __syncthreads();
+    double eb = 0.0;
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {
+        const int c = (t >> 6) + u * (kBlock / 64), j = cb * kT + c;
+        double w = 0.0;
+        if (n <= N && j < n) {
+            w = ldexp(g[u] * sYm[c] * iy, e[u] + sYe[c] - yn);
+            eb += w * (dd_diff(cn, {sC[c], sC[kT + c]}) + link3(a, el, sE + 3 * c));
+        }
+        sW[r * (kT + 1) + c] = w;
+    }
+    __syncthreads();
+    for (int q = t; q < kTT; q += kBlock) wt[q] = sW[(q >> 6) * (kT + 1) + (q & 63)];
+    __syncthreads();
+    sW[t] = eb;
+    __syncthreads();
+    if (t < kT) {
+        double x = sW[t];
+#pragma unroll
+        for (int u = 1; u < kBlock / 64; ++u) x += sW[u * 64 + t];
+        scr.eb[(size_t)tile * kT + t] = x;
+    }
+}
+
+struct AdjLds {
+    double wd[2][kTT];                      // the current and the next diagonal tile
+    double adj[kBosonMaxN + 1 + kT];
+    double pm[kSolveWaves][kT];
+};
+
+// Adjoints adj[j] = sum_{n>j} w[n,n-j] adj[n], adj[N] = 1, by blocks of 64
+// columns from the end, as k_boson_solve (lane c: column c; step r broadcasts
+// adj of row r); then V_B and EV_B = the inner energies + sum_n adj[n]
+// sum_k w[n,k] E'[n,k].
+__global__ __launch_bounds__(kSolve) void k_boson_adjoint(BosonArgs a)
+{
+    __shared__ AdjLds s;
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63, N = a.N;
+    const BosonScr scr(a);
+    if (scr.slow[0]) return;
+    const int nb = boson_blocks(N);
+    constexpr int W = kSolveWaves - 1;
+    constexpr int NB = (kT + W - 1) / W;
+    {
+        const size_t dg = (size_t)boson_tile(nb - 1, nb - 1) * kTT;
+        for (int e = t; e < kTT; e += kSolve) s.wd[(nb - 1) & 1][e] = scr.w[dg + e];
+    }
+    // adj beyond N counts nothing (its rows are zero); column N itself, when
+    // it starts a block of its own, is adj[N] = 1
+    for (int e = t; e < kBosonMaxN + 1 + kT; e += kSolve) s.adj[e] = (e == N) ? 1.0 : 0.0;
+    double acc = ((nb - 1) * kT + lane == N) ? 1.0 : 0.0;
+    __syncthreads();
+    for (int cb = nb - 1; cb >= 0; --cb) {
+        double bm[NB];
+        if (w == 0) {
+            __builtin_amdgcn_s_setprio(3);
+            const double *wd = s.wd[cb & 1];
+            acc += wd[(kT - 1) * kT + lane] * s.adj[(cb + 1) * kT];
+#pragma unroll 9
+            for (int r = kT - 2; r >= 0; --r) acc += wd[r * kT + lane] * lane_of(acc, r + 1);
+            __builtin_amdgcn_s_setprio(0);
+            s.adj[cb * kT + lane] = acc;
+        } else if (cb > 0) {
+            const size_t dg = (size_t)boson_tile(cb - 1, cb - 1) * kTT;
+            for (int e = t - 64; e < kTT; e += 64 * W) s.wd[(cb - 1) & 1][e] = scr.w[dg + e];
+            acc = 0.0;
+            constexpr int U = 8;
+            const int rows = (nb - 1 - cb) * kT;      // rows of the blocks after cb
+            auto at = [&](int q) {
+                const int b = cb + 1 + (q >> 6);
+                return ((size_t)boson_tile(b, cb - 1) * kT + (q & 63)) * kT + lane;
+            };
+            for (int q0 = w - 1; q0 < rows; q0 += W * U) {
+                double g[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int q = q0 + u * W;
+                    g[u] = q < rows ? scr.w[at(q)] : 0.0;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int q = min(q0 + u * W, rows - 1);
+                    acc += g[u] * s.adj[(cb + 1) * kT + 1 + q];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int r = w - 1 + u * W;
+                bm[u] = r < kT ? scr.w[((size_t)boson_tile(cb, cb - 1) * kT + r) * kT + lane] : 0.0;
+            }
+        }
+        __syncthreads();
+        if (cb == 0) break;
+        if (w > 0) {
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                acc += bm[u] * s.adj[cb * kT + 1 + min(w - 1 + u * W, kT - 1)];
+            s.pm[w][lane] = acc;
+        }
+        __syncthreads();
+        if (w == 0) {
+            acc = 0.0;
+#pragma unroll
+            for (int u = 1; u <= W; ++u) acc += s.pm[u][lane];
+        }
+    }
+    for (int e = t; e <= N; e += kSolve) scr.adj[e] = s.adj[e];
+    double ev = 0.0, esum = inner_sum(a, scr, t);
+    if (t < N) {
+        const int b = t / kT;
+        double eb = 0.0;
+        for (int cb = 0; cb <= b; ++cb) eb += scr.eb[(size_t)boson_tile(b, cb) * kT + (t & 63)];
+        ev = s.adj[t + 1] * eb;
+    }
+    ev = wave_sum(ev);
+    esum = wave_sum(esum);
+    if (lane == 0) {
+        s.pm[0][w] = ev;
+        s.pm[1][w] = esum;
+    }
+    __syncthreads();
+    if (t == 0) {
+        for (int u = 1; u < kSolveWaves; ++u) {
+            ev += s.pm[0][u];
+            esum += s.pm[1][u];
+        }
+        const DD vb = dd_add1({scr.vp[0], scr.vp[1]}, esum);
+        a.res[0] = vb.hi + vb.lo;
+        a.res[1] = esum + ev;
+    }
+}
+
+// Row n, one wave: q[n,j] = adj[n] w[n,n-j], the probability of the closing
+// link n-1 -> j; S[n,j] = sum_{j' <= j} q[n,j'], the probability that particle
+// n-1's ring starts at j or before; the closing links' force on particle
+// n-1's last bead.  With prob, row n-1 of it gets the closing links and zeros
+// (its chain entry n is written by k_boson_cols).
+__global__ __launch_bounds__(kBlock) void k_boson_rows(BosonArgs a)
+{
+    const int lane = threadIdx.x & 63, N = a.N;
+    const int n = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6) + 1;
+    if (n > N) return;
+    const BosonScr scr(a);
+    constexpr int NT = kBosonMaxN / kT;
+    const double an = scr.adj[n];
+    const size_t base = w_at(n, 0) + lane;
+    const double k2 = 2.0 * a.ks;
+    double el[3], g[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) el[d] = scr.el[(n - 1) * 3 + d];
+    double carry = 0.0;
+    constexpr int U = 4;
+    for (int c0 = 0; c0 * kT < n; c0 += U) {
+        double q[U], sc[U], x0[U][3];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = (c0 + u) * kT + lane;
+            q[u] = j < n ? an * scr.w[base + (size_t)(c0 + u) * kTT] : 0.0;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) x0[u][d] = j < n ? scr.e0[j * 3 + d] : 0.0;
         }
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            a.f[bidx(a, Pl, l, d)] += g[d];
-            a.f[bidx(a, 0, l, d)] += h[d];
+        for (int u = 0; u < U; ++u) {
+            const int j = (c0 + u) * kT + lane;
+            if (j < n)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) g[d] += k2 * q[u] * mic(x0[u][d], el[d], a.box[d]);
+            sc[u] = q[u];
         }
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const double v = __shfl_up(sc[u], o);
+                if (lane >= o) sc[u] += v;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = (c0 + u) * kT + lane;
+            if (j < n) {
+                scr.s[base + (size_t)(c0 + u) * kTT] = carry + sc[u];
+                if (a.prob) a.prob[(size_t)(n - 1) * N + j] = q[u];
+            } else if (a.prob && j < N) {
+                a.prob[(size_t)(n - 1) * N + j] = 0.0;
+            }
+            carry += __shfl(sc[u], 63);
+        }
+    }
+    static_assert(NT % U == 0, "whole groups of tiles");
+    if (a.prob)
+        for (int j = ((n + U * kT - 1) / (U * kT)) * (U * kT) + lane; j < N; j += 64)
+            a.prob[(size_t)(n - 1) * N + j] = 0.0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) g[d] = wave_sum(g[d]);
+    if (lane == 0) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) a.f[bidx(a, a.P - 1, n - 1, d)] += g[d];
+    }
+}
+
+// Column l: the chain link's probability chain[l] = sum_{n>=l+2} S[n,l] (the
+// rings in which l -> l+1 is a link) and the closing links' force on particle
+// l's first bead; then the chain links' forces.  A block takes 15 particles and
+// the one before them, 16 lanes wide so that a row is read in 128-byte pieces;
+// thread (row r of the row blocks, column).
+constexpr int kColBlock = 1024;
+constexpr int kColLanes = 16;
+__global__ __launch_bounds__(kColBlock) void k_boson_cols(BosonArgs a)
+{
+    constexpr int NW = kColBlock / 64;
+    __shared__ double red[NW][4][kColLanes];
+    const int t = threadIdx.x, c = t & (kColLanes - 1), r = t / kColLanes, N = a.N;
+    static_assert(kColBlock / kColLanes == kT, "one row of each row block per thread");
+    const int l = (int)blockIdx.x * (kColLanes - 1) - 1 + c;
+    const bool in = l >= 0 && l < N;
+    const BosonScr scr(a);
+    const int nb = boson_blocks(N), cb = in ? l / kT : nb;
+    const double k2 = 2.0 * a.ks;
+    double e0[3] = {0.0, 0.0, 0.0}, v[4] = {0.0, 0.0, 0.0, 0.0};
+    if (in)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) e0[d] = scr.e0[l * 3 + d];
+#pragma unroll 4
+    for (int b = cb; b < nb; ++b) {
+        const int n = b * kT + 1 + r;
+        if (n > N || l >= n) continue;
+        const size_t at = ((size_t)boson_tile(b, cb) * kT + r) * kT + (l - cb * kT);
+        const double q = scr.adj[n] * scr.w[at];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) v[d] -= k2 * q * mic(e0[d], scr.el[(n - 1) * 3 + d], a.box[d]);
+        if (n >= l + 2) v[3] += scr.s[at];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        v[q] += __shfl_xor(v[q], 16);
+        v[q] += __shfl_xor(v[q], 32);
+        if ((t & 63) < kColLanes) red[t >> 6][q][c] = v[q];
+    }
+    __syncthreads();
+    if (t >= 4 * kColLanes) return;
+    // one sum per thread, in wave order
+    const int q = t / kColLanes;
+    double x = red[0][q][c];
+    for (int u = 1; u < NW; ++u) x += red[u][q][c];
+    __builtin_amdgcn_wave_barrier();
+    red[0][q][c] = x;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    if (t < 1 || t >= kColLanes || !in) return;
+    const double cl = red[0][3][c], cm = red[0][3][c - 1];
+    double g[3] = {0.0, 0.0, 0.0}, h[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        h[d] = red[0][d][c];
+        if (l + 1 < N) g[d] = k2 * cl * mic(scr.e0[(l + 1) * 3 + d], scr.el[l * 3 + d], a.box[d]);
+        if (l >= 1) h[d] -= k2 * cm * mic(e0[d], scr.el[(l - 1) * 3 + d], a.box[d]);
+    }
+    if (a.prob && l + 1 < N) a.prob[(size_t)l * N + l + 1] = cl;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        a.f[bidx(a, a.P - 1, l, d)] += g[d];
+        a.f[bidx(a, 0, l, d)] += h[d];
     }
 }
 
@@ -737,10 +1324,14 @@ void launch_boson_trap(const FusedArgs &a, double *f, double *fpartials, hipStre
 
 void launch_boson_springs(const BosonArgs &a, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_boson_inner, dim3((a.N + kBlock - 1) / kBlock), dim3(kBlock), 0, st, a);
-    hipLaunchKernelGGL(k_boson_seq, dim3(1), dim3(kSeq), 0, st, a);
-    hipLaunchKernelGGL(k_boson_rows, dim3(a.N), dim3(kBlock), 0, st, a);
-    hipLaunchKernelGGL(k_boson_links, dim3((a.N + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0,
+    const int tiles = boson_tiles(a.N), inner = inner_blocks(a.N, a.P);
+    hipLaunchKernelGGL(k_boson_prep, dim3(tiles + inner + 1), dim3(kBlock), 0, st, a);
+    hipLaunchKernelGGL(k_boson_solve, dim3(1), dim3(kSolve), 0, st, a);
+    hipLaunchKernelGGL(k_boson_weights, dim3(tiles), dim3(kBlock), 0, st, a);
+    hipLaunchKernelGGL(k_boson_adjoint, dim3(1), dim3(kSolve), 0, st, a);
+    hipLaunchKernelGGL(k_boson_rows, dim3((a.N + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0,
+                       st, a);
+    hipLaunchKernelGGL(k_boson_cols, dim3((a.N + kColLanes - 2) / (kColLanes - 1)), dim3(kColBlock), 0,
                        st, a);
 }
 

@@ -207,15 +207,26 @@ void launch_npt_a(const NptArgs &a, int mode, hipStream_t s);
 void launch_npt_b(const NptArgs &a, hipStream_t s);
 void launch_pair_npt(const PairArgs &a, int grid, hipStream_t s);
 
-// Bosonic exchange springs (pimd_boson.hip).  Scratch (doubles): the ring
-// weights w[n,k] and their probabilities' suffix sums T[n,k] (rows n = 1..N
-// of n entries each, row n at n(n-1)/2), the adjoints adj[0..N] and the
-// particles' inner spring energies eint[N].
-constexpr int kBosonMaxN = 1024;   // particles (the sequential kernel's LDS)
-constexpr __host__ __device__ inline size_t boson_scr_tri(int N) { return (size_t)N * (size_t)(N + 1) / 2; }
-constexpr __host__ __device__ inline size_t boson_scr_adj(int N) { return 2 * boson_scr_tri(N); }
-constexpr __host__ __device__ inline size_t boson_scr_eint(int N) { return boson_scr_adj(N) + (size_t)N + 1; }
-constexpr __host__ __device__ inline size_t boson_scr_doubles(int N) { return boson_scr_eint(N) + (size_t)N; }
+// Bosonic exchange springs (pimd_boson.hip).  Scratch, in doubles: the ring
+// weights in 64 x 64 tiles of (row n, column j = n - k), j < n (boson_tile);
+// their running probabilities, likewise (earlier in the same call, the
+// exponents of the exchange factors); then the vectors, in the order of
+// BosonScr.
+constexpr int kBosonMaxN = 1024;   // particles (the sequential kernels' LDS)
+constexpr int kBosonTile = 64;     // tile side: the lanes of a wave
+constexpr int kBosonInnerMax = 256;   // blocks (and partial energies) of the inner springs
+constexpr __host__ __device__ inline int boson_blocks(int N) { return (N + kBosonTile - 1) / kBosonTile; }
+constexpr __host__ __device__ inline int boson_tile(int b, int cb) { return b * (b + 1) / 2 + cb; }
+constexpr __host__ __device__ inline int boson_tiles(int N) { return boson_tile(boson_blocks(N), 0); }
+constexpr __host__ __device__ inline size_t boson_scr_tri(int N)
+{
+    return (size_t)boson_tiles(N) * kBosonTile * kBosonTile;
+}
+constexpr __host__ __device__ inline size_t boson_scr_doubles(int N)
+{
+    return 2 * boson_scr_tri(N) + 13 * ((size_t)N + 1) + (size_t)boson_tiles(N) * (kBosonTile + 1) +
+           kBosonInnerMax + 4;
+}
 struct BosonArgs {
     const double *x;     // positions
     int N, P;

@@ -357,7 +357,7 @@ int pimd_set_barostat(pimd_ctx *ctx, const double *box, const double *vw);
  * receives the spring forces -dV_B/dx; prob ([N][N], device, or NULL) the
  * probability that bead P-1 of particle l links to bead 0 of particle l'.
  * Work is enqueued on stream (a hipStream_t; NULL = the null stream); the
- * call allocates its scratch (about 8 N^2 bytes), waits for the stream and
+ * call allocates its scratch (about 9 N^2 bytes), waits for the stream and
  * frees it before it returns.
  * Errors: ARG (NULL x, f or out, N < 1, P < 1, kspring < 0 or not finite,
  * beta_n <= 0, a negative or non-finite box length), UNSUPPORTED (N > 1024,
@@ -369,7 +369,7 @@ int pimd_boson_spring(const double *x, int32_t N, int32_t P, double kspring, dou
  * device memory: code under hipGraph capture, tight serving loops, harnesses
  * that forbid hipMalloc.  Same arguments, results and errors as
  * pimd_boson_spring, for N <= 512 (UNSUPPORTED above).  Its scratch is a
- * static device array of 2.1 MB per device, held until the process ends and
+ * static device array of 2.4 MB per device, held until the process ends and
  * looked up (hipGetSymbolAddress) at the first call on each device.  The call
  * enqueues its kernels on stream and returns without waiting.  All calls on a
  * device share that device's scratch, which keeps the last call's contents

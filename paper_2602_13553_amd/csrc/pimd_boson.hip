@@ -54,7 +54,7 @@
 namespace pimd {
 
 // The allocation-free entry point's scratch (pimd_boson_spring_noalloc): one
-// copy per device, 2.1 MB, held until the process ends.  Host code reaches it
+// copy per device, 2.4 MB, held until the process ends.  Host code reaches it
 // only through the per-device address from hipGetSymbolAddress (in host code
 // the array's name is a host-side stand-in, not a device address).
 constexpr int kBosonNoAllocMaxN = 512;
@@ -76,10 +76,13 @@ constexpr int kNoExp = -(1 << 30);   // exponent of an exact zero
 
 // Scratch (see pimd_internal.h)
 struct BosonScr {
-    double *w;      // [tiles][64 rows n][64 columns j] ring weights; first
-                    // [tiles][64 columns][64 rows] mantissas of the matrix
-    double *s;      // [tiles][64][64] running probabilities over j
-    int *ge;        // [tiles][64 columns][64 rows] exponents (in s's place)
+    // Tiles are laid out for 16 bytes per lane and load: a CU takes a wave's
+    // load every 17 cycles whether its lanes load 4, 8 or 16 bytes.
+    double *w;      // [tiles][32 row pairs][64 columns j][2 rows n] ring weights;
+                    // first [tiles][32 column pairs][64 rows][2] mantissas of
+                    // the matrix
+    double *s;      // like w: running probabilities over j
+    int *ge;        // [tiles][16][64 rows][4 columns] exponents (in s's place)
     double *ym;     // [N+1] Y: mantissa in [0.5, 1), exponent
     int *ye;
     double *xm;     // [N+1] exp(beta_n L[n-1,n]) (1 for n = N), likewise
@@ -121,7 +124,7 @@ struct BosonScr {
 __device__ __forceinline__ size_t w_at(int n, int j)
 {
     const int b = (n - 1) / kT, r = (n - 1) - b * kT, cb = j / kT;
-    return ((size_t)boson_tile(b, cb) * kT + r) * kT + (j - cb * kT);
+    return (size_t)boson_tile(b, cb) * kTT + ((r >> 1) * kT + (j - cb * kT)) * 2 + (r & 1);
 }
 
 __device__ __forceinline__ size_t bidx(const BosonArgs &a, int j, int l, int d)
@@ -415,12 +418,12 @@ __device__ __forceinline__ double link3(const BosonArgs &a, const double *el, co
 }
 
 // Blocks 0..tiles-1: the matrix exp(beta_n (L[n-1,n] - L[n-1,j])) / n, one
-// 64 x 64 tile each (column by column, a row per lane: the order in which the
-// solve reads it).  Then the inner springs (forces on every bead, overwriting
+// 64 x 64 tile each (columns in order, a row per lane: as the solve reads it).  Then the inner springs (forces on every bead, overwriting
 // f, elementwise so that either layout is read in order; one partial energy per
 // block).  The last block: the particles' end beads, packed, and the chain
-// links' prefix sums.  N = 1024, P = 32: 7 us (the inner springs alone took
-// 38 us with a thread per particle, whose reads are a bead row apart).
+// links' prefix sums.  13 us at N = 1024, P = 32 (the inner springs alone took
+// 38 us with a thread per particle, whose reads are a bead row apart), bound
+// by the tiles' exponentials and the launch.
 __global__ __launch_bounds__(kBlock) void k_boson_prep(BosonArgs a)
 {
     __shared__ double sh[2 * kBlock];
@@ -461,26 +464,32 @@ __global__ __launch_bounds__(kBlock) void k_boson_prep(BosonArgs a)
         }
         const double hm = xm / (double)n;
         __syncthreads();
-        double *gm = scr.w + (size_t)tile * kTT;
-        int *ge = scr.ge + (size_t)tile * kTT;
-        for (int c = t >> 6; c < kT; c += kBlock / 64) {
-            const int j = cb * kT + c;
-            double m = 0.0;
-            int e = kNoExp;
-            if (n <= N && j < n) {
-                const double L = link3(a, el, sh + 3 * c), p = a.bn * L;
-                if (p <= kWideLink) {
-                    int k;
-                    exp_ext(-p, -fma(a.bn, L, -p), m, k);
-                    m *= hm;
-                    e = k + xe + __builtin_amdgcn_frexp_exp(m);
-                    m = __builtin_amdgcn_frexp_mant(m);
-                } else {
-                    bad = true;
+        double2 *gm = reinterpret_cast<double2 *>(scr.w + (size_t)tile * kTT);
+        int4 *ge = reinterpret_cast<int4 *>(scr.ge + (size_t)tile * kTT);
+        for (int q = t >> 6; q < kT / 4; q += kBlock / 64) {
+            double m[4];
+            int e[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int c = 4 * q + u, j = cb * kT + c;
+                m[u] = 0.0;
+                e[u] = kNoExp;
+                if (n <= N && j < n) {
+                    const double L = link3(a, el, sh + 3 * c), p = a.bn * L;
+                    if (p <= kWideLink) {
+                        int k;
+                        exp_ext(-p, -fma(a.bn, L, -p), m[u], k);
+                        m[u] *= hm;
+                        e[u] = k + xe + __builtin_amdgcn_frexp_exp(m[u]);
+                        m[u] = __builtin_amdgcn_frexp_mant(m[u]);
+                    } else {
+                        bad = true;
+                    }
                 }
             }
-            gm[c * kT + r] = m;
-            ge[c * kT + r] = e;
+            gm[(2 * q) * kT + r] = make_double2(m[0], m[1]);
+            gm[(2 * q + 1) * kT + r] = make_double2(m[2], m[3]);
+            ge[q * kT + r] = make_int4(e[0], e[1], e[2], e[3]);
         }
         const int any = __syncthreads_or(bad ? 1 : 0);
         if (t == 0) scr.wide[tile] = any;
@@ -512,7 +521,7 @@ __global__ __launch_bounds__(kBlock) void k_boson_prep(BosonArgs a)
     }
     // end beads, and the prefix sums ch[m] = sum_{l<m} link(l, l+1), m = 0..N-1,
     // in double-double: each thread sums a contiguous chunk, the chunk totals
-    // are scanned (Hillis-Steele), then each chunk is written out
+    // are scanned in the waves and across them, then each chunk is written out
     for (int e = t; e < N * 3; e += kBlock) {
         const int l = e / 3, d = e - l * 3;
         scr.e0[e] = a.x[bidx(a, 0, l, d)];
@@ -539,23 +548,22 @@ __global__ __launch_bounds__(kBlock) void k_boson_prep(BosonArgs a)
             tot = dd_add1(tot, L[u]);
         }
     }
-    double *hi = sh, *lo = sh + kBlock;
-    hi[t] = tot.hi;
-    lo[t] = tot.lo;
-    __syncthreads();
-    for (int off = 1; off < kBlock; off <<= 1) {
-        DD add = {0.0, 0.0};
-        if (t >= off) add = {hi[t - off], lo[t - off]};
-        __syncthreads();
-        if (t >= off) {
-            const DD v = dd_add({hi[t], lo[t]}, add);
-            hi[t] = v.hi;
-            lo[t] = v.lo;
-        }
-        __syncthreads();
+    const int lane = t & 63, w = t >> 6;
+    DD inc = tot;                                    // scan of the wave's chunk totals
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const DD v = {__shfl_up(inc.hi, off), __shfl_up(inc.lo, off)};
+        if (lane >= off) inc = dd_add(v, inc);
     }
-    DD run = {0.0, 0.0};
-    if (t > 0) run = {hi[t - 1], lo[t - 1]};
+    if (lane == 63) {
+        sh[2 * w] = inc.hi;
+        sh[2 * w + 1] = inc.lo;
+    }
+    __syncthreads();
+    DD run = {0.0, 0.0};                             // everything before this thread's chunk
+    for (int u = 0; u < w; ++u) run = dd_add(run, {sh[2 * u], sh[2 * u + 1]});
+    const DD ex = {__shfl_up(inc.hi, 1), __shfl_up(inc.lo, 1)};
+    if (lane > 0) run = dd_add(run, ex);
     if (t == 0) {
         scr.chi[0] = 0.0;
         scr.clo[0] = 0.0;
@@ -581,39 +589,65 @@ __device__ __forceinline__ double lane_of(double v, int lane)
 }
 
 struct SolveLds {
-    double gm[2][kTT];              // the current and the next diagonal tile
-    int ge[2][kTT];
+    double2 gm[2][kTT / 2];         // the current and the next diagonal tile
+    int4 ge[2][kTT / 4];
     double ym[kBosonMaxN + 1];      // Y
     int ye[kBosonMaxN + 1];
-    double pm[kSolveWaves][kT];       // the waves' sums over the columns before the block
+    double pm[kSolveWaves][kT];     // the waves' sums over the columns before the block
     int pe[kSolveWaves][kT];
 };
+
+// four columns of a tile for one row (lane): mantissas and exponents
+struct Quad {
+    double2 a, b;
+    int4 e;
+};
+__device__ __forceinline__ Quad quad_at(const double2 *gm, const int4 *ge, int q, int lane)
+{
+    return {gm[2 * q * kT + lane], gm[(2 * q + 1) * kT + lane], ge[q * kT + lane]};
+}
+// += those columns times Y
+__device__ __forceinline__ void quad_add(double &am, int &ae, const Quad &g, const double *ym,
+                                         const int *ye)
+{
+    ext_add(am, ae, g.a.x * ym[0], g.e.x + ye[0]);
+    ext_add(am, ae, g.a.y * ym[1], g.e.y + ye[1]);
+    ext_add(am, ae, g.b.x * ym[2], g.e.z + ye[2]);
+    ext_add(am, ae, g.b.y * ym[3], g.e.w + ye[3]);
+}
 
 // The triangular system, one block, by blocks of 64 rows.  Wave 0 solves the
 // diagonal tile: lane r holds row r's sum, and step c broadcasts the Y that
 // lane c-1 has just finished, so a step is one broadcast and one multiply-add
-// of (mantissa, exponent) deep.  Meanwhile waves 1..15 sum the next block's
-// rows over the columns known so far, and once the tile is solved they add its
-// 64 columns, fetched ahead.  Bound by the diagonal tiles' chain (64 steps)
-// and, at large N, by one CU's reads of the matrix (12 B per entry).
+// of (mantissa, exponent) deep (87 cycles, 2.3 us per block).  Meanwhile waves
+// 1..15 sum the next block's rows over the columns known so far, and once the
+// tile is solved every wave adds four of its 64 columns, fetched ahead.  Bound
+// by the diagonal tiles' chain and, at large N, by one CU's reads of the matrix
+// (12 B per entry; one CU reads 107 GB/s from beyond its L2, half of that with
+// 8-byte lanes).  88 us at N = 1024, 35 us at N = 512; with 8- and 4-byte lanes
+// 127 and 45 us, and the recursion in log space, adjoint included, 2683 and
+// 1125 us.
 __global__ __launch_bounds__(kSolve) void k_boson_solve(BosonArgs a)
 {
     __shared__ SolveLds s;
-    const int t = threadIdx.x, w = t >> 6, lane = t & 63, N = a.N;
+    const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63, N = a.N;
     const BosonScr scr(a);
     const int nb = boson_blocks(N), tiles = boson_tiles(N);
+    const double2 *gmat = reinterpret_cast<const double2 *>(scr.w);
+    const int4 *gexp = reinterpret_cast<const int4 *>(scr.ge);
+    const double2 dm0 = gmat[t], dm1 = gmat[t + kSolve];
+    const int4 de0 = gexp[t];
     const int slow = __syncthreads_or(t < tiles ? scr.wide[t] : 0);
     static_assert(boson_tiles(kBosonMaxN) <= kSolve, "one flag per thread");
     if (t == 0) scr.slow[0] = slow ? 1 : 0;
     if (slow) return;                            // k_boson_weights runs seq_recursion
-    constexpr int W = kSolveWaves - 1;             // waves that sum ahead
-    constexpr int NB = (kT + W - 1) / W;         // columns of the last block per such wave
+    constexpr int W = kSolveWaves - 1;           // waves that sum ahead
+    static_assert(kT / 4 == kSolveWaves, "every wave takes four of a tile's columns");
     double am = 0.0;
     int ae = kNoExp;
-    for (int e = t; e < kTT; e += kSolve) {
-        s.gm[0][e] = scr.w[e];
-        s.ge[0][e] = scr.ge[e];
-    }
+    s.gm[0][t] = dm0;
+    s.gm[0][t + kSolve] = dm1;
+    s.ge[0][t] = de0;
     if (t == 0) {
         s.ym[0] = 0.5;
         s.ye[0] = 1;
@@ -622,18 +656,30 @@ __global__ __launch_bounds__(kSolve) void k_boson_solve(BosonArgs a)
     }
     __syncthreads();
     for (int b = 0; b < nb; ++b) {
-        double bm[NB];
-        int be[NB];
+        Quad last = {};                          // four of the columns [64 b, 64 b + 64) of block b+1
+        const double2 *rm = gmat + (size_t)boson_tile(b + 1, 0) * (kTT / 2);
+        const int4 *re = gexp + (size_t)boson_tile(b + 1, 0) * (kTT / 4);
+        if (b + 1 < nb) last = quad_at(rm, re, b * (kT / 4) + w, lane);
         if (w == 0) {
             __builtin_amdgcn_s_setprio(3);
-            const double *gm = s.gm[b & 1];
-            const int *ge = s.ge[b & 1];
-            ext_add(am, ae, gm[lane] * s.ym[b * kT], ge[lane] + s.ye[b * kT]);
-#pragma unroll 9
-            for (int c = 1; c < kT; ++c) {
-                const double ym = lane_of(am, c - 1);
-                const int ye = __builtin_amdgcn_readlane(ae, c - 1);
-                ext_add(am, ae, gm[c * kT + lane] * ym, ge[c * kT + lane] + ye);
+            const double2 *gm = s.gm[b & 1];
+            const int4 *ge = s.ge[b & 1];
+            double ym = s.ym[b * kT];
+            int ye = s.ye[b * kT];
+            Quad g = quad_at(gm, ge, 0, lane);
+#pragma unroll 2
+            for (int q = 0; q < kT / 4; ++q) {
+                const Quad gn = quad_at(gm, ge, min(q + 1, kT / 4 - 1), lane);
+                ext_add(am, ae, g.a.x * ym, g.e.x + ye);
+                ext_add(am, ae, g.a.y * lane_of(am, 4 * q),
+                        g.e.y + __builtin_amdgcn_readlane(ae, 4 * q));
+                ext_add(am, ae, g.b.x * lane_of(am, 4 * q + 1),
+                        g.e.z + __builtin_amdgcn_readlane(ae, 4 * q + 1));
+                ext_add(am, ae, g.b.y * lane_of(am, 4 * q + 2),
+                        g.e.w + __builtin_amdgcn_readlane(ae, 4 * q + 2));
+                ym = lane_of(am, 4 * q + 3);
+                ye = __builtin_amdgcn_readlane(ae, 4 * q + 3);
+                g = gn;
             }
             __builtin_amdgcn_s_setprio(0);
             const int n = b * kT + 1 + lane;
@@ -645,58 +691,67 @@ __global__ __launch_bounds__(kSolve) void k_boson_solve(BosonArgs a)
                 scr.ym[n] = m;
                 scr.ye[n] = e;
             }
-        } else if (b + 1 < nb) {
-            const size_t row = (size_t)boson_tile(b + 1, 0) * kTT + lane;
-            const size_t dg = (size_t)boson_tile(b + 1, b + 1) * kTT;
-            for (int e = t - 64; e < kTT; e += 64 * W) {
-                s.gm[(b + 1) & 1][e] = scr.w[dg + e];
-                s.ge[(b + 1) & 1][e] = scr.ge[dg + e];
-            }
             am = 0.0;
             ae = kNoExp;
-            constexpr int U = 8;
-            for (int j0 = w - 1; j0 < b * kT; j0 += W * U) {
-                double g[U];
-                int e[U];
+        } else if (b + 1 < nb) {
+            // the next diagonal tile in flight while the columns known so far
+            // are summed (the next group's reads ahead of this group's sums)
+            const double2 *dg = rm + (b + 1) * (kTT / 2);
+            const int4 *dh = re + (b + 1) * (kTT / 4);
+            constexpr int ND = (kTT / 2 + 64 * W - 1) / (64 * W), NE = (kTT / 4 + 64 * W - 1) / (64 * W);
+            double2 dm[ND];
+            int4 de[NE];
+#pragma unroll
+            for (int u = 0; u < ND; ++u) dm[u] = dg[min(t - 64 + u * 64 * W, kTT / 2 - 1)];
+#pragma unroll
+            for (int u = 0; u < NE; ++u) de[u] = dh[min(t - 64 + u * 64 * W, kTT / 4 - 1)];
+            am = 0.0;
+            ae = kNoExp;
+            constexpr int U = 1;
+            const int J = b * (kT / 4);           // groups of four columns before them
+            Quad g[2][U];
+            auto fetch = [&](int h, int j0) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) g[h][u] = quad_at(rm, re, min(j0 + u * W, J - 1), lane);
+            };
+            auto add = [&](int h, int j0) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int j = j0 + u * W;
-                    const bool in = j < b * kT;
-                    g[u] = in ? scr.w[row + (size_t)j * kT] : 0.0;
-                    e[u] = in ? scr.ge[row + (size_t)j * kT] : kNoExp;
+                    if (j < J) quad_add(am, ae, g[h][u], s.ym + 4 * j, s.ye + 4 * j);
                 }
+            };
+            if (w - 1 < J) fetch(0, w - 1);
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int j = min(j0 + u * W, b * kT - 1);
-                    ext_add(am, ae, g[u] * s.ym[j], e[u] + s.ye[j]);
-                }
+            for (int u = 0; u < ND; ++u) {
+                const int q = t - 64 + u * 64 * W;
+                if (q < kTT / 2) s.gm[(b + 1) & 1][q] = dm[u];
             }
 #pragma unroll
-            for (int u = 0; u < NB; ++u) {
-                const int c = w - 1 + u * W;
-                bm[u] = c < kT ? scr.w[row + (size_t)(b * kT + c) * kT] : 0.0;
-                be[u] = c < kT ? scr.ge[row + (size_t)(b * kT + c) * kT] : kNoExp;
+            for (int u = 0; u < NE; ++u) {
+                const int q = t - 64 + u * 64 * W;
+                if (q < kTT / 4) s.ge[(b + 1) & 1][q] = de[u];
+            }
+            for (int j0 = w - 1; j0 < J; j0 += 2 * W * U) {
+                if (j0 + W * U < J) fetch(1, j0 + W * U);
+                add(0, j0);
+                if (j0 + 2 * W * U < J) fetch(0, j0 + 2 * W * U);
+                if (j0 + W * U < J) add(1, j0 + W * U);
             }
         }
         __syncthreads();
         if (b + 1 == nb) break;
-        if (w > 0) {
-#pragma unroll
-            for (int u = 0; u < NB; ++u) {
-                const int j = b * kT + min(w - 1 + u * W, kT - 1);
-                ext_add(am, ae, bm[u] * s.ym[j], be[u] + s.ye[j]);
-            }
-            s.pm[w][lane] = am;
-            s.pe[w][lane] = ae;
-        }
+        quad_add(am, ae, last, s.ym + b * kT + 4 * w, s.ye + b * kT + 4 * w);
+        s.pm[w][lane] = am;
+        s.pe[w][lane] = ae;
         __syncthreads();
         if (w == 0) {
             int e = kNoExp;
 #pragma unroll
-            for (int u = 1; u <= W; ++u) e = max(e, s.pe[u][lane]);
+            for (int u = 0; u < kSolveWaves; ++u) e = max(e, s.pe[u][lane]);
             am = 0.0;
 #pragma unroll
-            for (int u = 1; u <= W; ++u) am += ldexp(s.pm[u][lane], s.pe[u][lane] - e);
+            for (int u = 0; u < kSolveWaves; ++u) am += ldexp(s.pm[u][lane], s.pe[u][lane] - e);
             ae = e;
         }
     }
@@ -734,7 +789,7 @@ struct WeightLds {
 };
 
 // Ring weights of one tile, w[n,k] = G[n,j] Y[j] / Y[n] (j = n - k), written
-// row by row (the order in which the adjoint and the links read them), and the
+// by row pairs (the order in which the adjoint and the links read them), and the
 // tile's share of each row's sum_k w[n,k] E'[n,k].  A call that the solve left
 // runs the recursion in log space here instead (block 0).
 __global__ __launch_bounds__(kBlock) void k_boson_weights(BosonArgs a)
@@ -744,25 +799,20 @@ __global__ __launch_bounds__(kBlock) void k_boson_weights(BosonArgs a)
     int *sYe = lds.v.ye;
     const int t = threadIdx.x, N = a.N, tile = blockIdx.x;
     const BosonScr scr(a);
-    if (scr.slow[0]) {
-        if (tile == 0) seq_recursion(a, lds.q);
-        return;
-    }
     int b = (int)((sqrtf(8.0f * (float)tile + 1.0f) - 1.0f) * 0.5f);
     while (boson_tile(b + 1, 0) <= tile) ++b;
     while (boson_tile(b, 0) > tile) --b;
     const int cb = tile - boson_tile(b, 0);
     const int r = t & 63, n = b * kT + 1 + r;
-    double *wt = scr.w + (size_t)tile * kTT;
-    const int *ge = scr.ge + (size_t)tile * kTT;
-    constexpr int NC = kT / (kBlock / 64);
-    double g[NC];
-    int e[NC];
+    double2 *wt = reinterpret_cast<double2 *>(scr.w + (size_t)tile * kTT);
+    const int4 *ge = reinterpret_cast<const int4 *>(scr.ge + (size_t)tile * kTT);
+    constexpr int NQ = kT / 4 / (kBlock / 64);
+    Quad g[NQ];
 #pragma unroll
-    for (int u = 0; u < NC; ++u) {
-        const int c = (t >> 6) + u * (kBlock / 64);
-        g[u] = wt[c * kT + r];
-        e[u] = ge[c * kT + r];
+    for (int u = 0; u < NQ; ++u) g[u] = quad_at(wt, ge, (t >> 6) + u * (kBlock / 64), r);
+    if (scr.slow[0]) {
+        if (tile == 0) seq_recursion(a, lds.q);
+        return;
     }
     if (t < 3 * kT) sE[t] = cb * kT + t / 3 < N ? scr.e0[cb * kT * 3 + t] : 0.0;
     if (t < kT && cb * kT + t < N) {
@@ -784,17 +834,26 @@ __global__ __launch_bounds__(kBlock) void k_boson_weights(BosonArgs a)
     __syncthreads();
     double eb = 0.0;
 #pragma unroll
-    for (int u = 0; u < NC; ++u) {
-        const int c = (t >> 6) + u * (kBlock / 64), j = cb * kT + c;
-        double w = 0.0;
-        if (n <= N && j < n) {
-            w = ldexp(g[u] * sYm[c] * iy, e[u] + sYe[c] - yn);
-            eb += w * (dd_diff(cn, {sC[c], sC[kT + c]}) + link3(a, el, sE + 3 * c));
+    for (int u = 0; u < NQ; ++u) {
+        const int c0 = 4 * ((t >> 6) + u * (kBlock / 64));
+        const double gm[4] = {g[u].a.x, g[u].a.y, g[u].b.x, g[u].b.y};
+        const int gx[4] = {g[u].e.x, g[u].e.y, g[u].e.z, g[u].e.w};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int c = c0 + v;
+            double w = 0.0;
+            if (n <= N && cb * kT + c < n) {
+                w = ldexp(gm[v] * sYm[c] * iy, gx[v] + sYe[c] - yn);
+                eb += w * (dd_diff(cn, {sC[c], sC[kT + c]}) + link3(a, el, sE + 3 * c));
+            }
+            sW[r * (kT + 1) + c] = w;
         }
-        sW[r * (kT + 1) + c] = w;
     }
     __syncthreads();
-    for (int q = t; q < kTT; q += kBlock) wt[q] = sW[(q >> 6) * (kT + 1) + (q & 63)];
+    for (int q = t; q < kTT / 2; q += kBlock) {
+        const double *w2 = sW + 2 * (q >> 6) * (kT + 1) + (q & 63);
+        wt[q] = make_double2(w2[0], w2[kT + 1]);
+    }
     __syncthreads();
     sW[t] = eb;
     __syncthreads();
@@ -807,27 +866,31 @@ __global__ __launch_bounds__(kBlock) void k_boson_weights(BosonArgs a)
 }
 
 struct AdjLds {
-    double wd[2][kTT];                      // the current and the next diagonal tile
+    double2 wd[2][kTT / 2];                 // the current and the next diagonal tile
     double adj[kBosonMaxN + 1 + kT];
     double pm[kSolveWaves][kT];
 };
 
 // Adjoints adj[j] = sum_{n>j} w[n,n-j] adj[n], adj[N] = 1, by blocks of 64
-// columns from the end, as k_boson_solve (lane c: column c; step r broadcasts
-// adj of row r); then V_B and EV_B = the inner energies + sum_n adj[n]
-// sum_k w[n,k] E'[n,k].
+// columns from the end, as k_boson_solve (lane c: column c; a step broadcasts
+// the adj of the row before, 47 cycles); then V_B and EV_B = the inner energies
+// + sum_n adj[n] sum_k w[n,k] E'[n,k].  72 us at N = 1024, 25 us at N = 512, bound
+// as the solve.
 __global__ __launch_bounds__(kSolve) void k_boson_adjoint(BosonArgs a)
 {
     __shared__ AdjLds s;
-    const int t = threadIdx.x, w = t >> 6, lane = t & 63, N = a.N;
+    const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63, N = a.N;
     const BosonScr scr(a);
-    if (scr.slow[0]) return;
     const int nb = boson_blocks(N);
     constexpr int W = kSolveWaves - 1;
-    constexpr int NB = (kT + W - 1) / W;
+    constexpr int NL = kT / 2 / kSolveWaves;       // row pairs of the last block per wave
+    const double2 *wm = reinterpret_cast<const double2 *>(scr.w);
     {
-        const size_t dg = (size_t)boson_tile(nb - 1, nb - 1) * kTT;
-        for (int e = t; e < kTT; e += kSolve) s.wd[(nb - 1) & 1][e] = scr.w[dg + e];
+        const double2 *dg = wm + (size_t)boson_tile(nb - 1, nb - 1) * (kTT / 2);
+        const double2 d0 = dg[t], d1 = dg[t + kSolve];
+        if (scr.slow[0]) return;
+        s.wd[(nb - 1) & 1][t] = d0;
+        s.wd[(nb - 1) & 1][t + kSolve] = d1;
     }
     // adj beyond N counts nothing (its rows are zero); column N itself, when
     // it starts a block of its own, is adj[N] = 1
@@ -835,57 +898,88 @@ __global__ __launch_bounds__(kSolve) void k_boson_adjoint(BosonArgs a)
     double acc = ((nb - 1) * kT + lane == N) ? 1.0 : 0.0;
     __syncthreads();
     for (int cb = nb - 1; cb >= 0; --cb) {
-        double bm[NB];
+        // row pairs of the tile (cb, cb-1): rows 64 cb + 1 .. 64 cb + 64
+        double2 last[NL] = {};
+        if (cb > 0) {
+            const double2 *lt = wm + (size_t)boson_tile(cb, cb - 1) * (kTT / 2);
+#pragma unroll
+            for (int u = 0; u < NL; ++u) last[u] = (lt + (w * NL + u) * kT)[lane];
+        }
         if (w == 0) {
             __builtin_amdgcn_s_setprio(3);
-            const double *wd = s.wd[cb & 1];
-            acc += wd[(kT - 1) * kT + lane] * s.adj[(cb + 1) * kT];
-#pragma unroll 9
-            for (int r = kT - 2; r >= 0; --r) acc += wd[r * kT + lane] * lane_of(acc, r + 1);
+            const double2 *wd = s.wd[cb & 1];
+            double x = s.adj[(cb + 1) * kT];
+            constexpr int G = 4;                 // row pairs read ahead
+            double2 g[G];
+#pragma unroll
+            for (int u = 0; u < G; ++u) g[u] = wd[(kT / 2 - 1 - u) * kT + lane];
+            for (int q = kT / 2 - 1; q >= 0; q -= G) {
+                double2 gn[G];
+#pragma unroll
+                for (int u = 0; u < G; ++u) gn[u] = wd[max(q - G - u, 0) * kT + lane];
+#pragma unroll
+                for (int u = 0; u < G; ++u) {
+                    acc = fma(g[u].y, x, acc);
+                    acc = fma(g[u].x, lane_of(acc, 2 * (q - u) + 1), acc);
+                    x = lane_of(acc, 2 * (q - u));
+                }
+#pragma unroll
+                for (int u = 0; u < G; ++u) g[u] = gn[u];
+            }
             __builtin_amdgcn_s_setprio(0);
             s.adj[cb * kT + lane] = acc;
-        } else if (cb > 0) {
-            const size_t dg = (size_t)boson_tile(cb - 1, cb - 1) * kTT;
-            for (int e = t - 64; e < kTT; e += 64 * W) s.wd[(cb - 1) & 1][e] = scr.w[dg + e];
             acc = 0.0;
-            constexpr int U = 8;
-            const int rows = (nb - 1 - cb) * kT;      // rows of the blocks after cb
-            auto at = [&](int q) {
-                const int b = cb + 1 + (q >> 6);
-                return ((size_t)boson_tile(b, cb - 1) * kT + (q & 63)) * kT + lane;
+        } else if (cb > 0) {
+            const double2 *dg = wm + (size_t)boson_tile(cb - 1, cb - 1) * (kTT / 2);
+            constexpr int ND = (kTT / 2 + 64 * W - 1) / (64 * W);
+            double2 dm[ND];
+#pragma unroll
+            for (int u = 0; u < ND; ++u) dm[u] = dg[min(t - 64 + u * 64 * W, kTT / 2 - 1)];
+            acc = 0.0;
+            constexpr int U = 4;
+            const int rows = (nb - 1 - cb) * (kT / 2);   // row pairs of the blocks after cb
+            double2 g[2][U];
+            auto fetch = [&](int h, int q0) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int q = min(q0 + u * W, rows - 1), b = cb + 1 + (q >> 5);
+                    g[h][u] = (wm + (size_t)boson_tile(b, cb - 1) * (kTT / 2) + (q & 31) * kT)[lane];
+                }
             };
-            for (int q0 = w - 1; q0 < rows; q0 += W * U) {
-                double g[U];
+            auto add = [&](int h, int q0) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int q = q0 + u * W;
-                    g[u] = q < rows ? scr.w[at(q)] : 0.0;
+                    const double *x = s.adj + (cb + 1) * kT + 1 + 2 * q;
+                    if (q < rows) acc += g[h][u].x * x[0] + g[h][u].y * x[1];
                 }
+            };
+            if (w - 1 < rows) fetch(0, w - 1);
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int q = min(q0 + u * W, rows - 1);
-                    acc += g[u] * s.adj[(cb + 1) * kT + 1 + q];
-                }
+            for (int u = 0; u < ND; ++u) {
+                const int q = t - 64 + u * 64 * W;
+                if (q < kTT / 2) s.wd[(cb - 1) & 1][q] = dm[u];
             }
-#pragma unroll
-            for (int u = 0; u < NB; ++u) {
-                const int r = w - 1 + u * W;
-                bm[u] = r < kT ? scr.w[((size_t)boson_tile(cb, cb - 1) * kT + r) * kT + lane] : 0.0;
+            for (int q0 = w - 1; q0 < rows; q0 += 2 * W * U) {
+                if (q0 + W * U < rows) fetch(1, q0 + W * U);
+                add(0, q0);
+                if (q0 + 2 * W * U < rows) fetch(0, q0 + 2 * W * U);
+                if (q0 + W * U < rows) add(1, q0 + W * U);
             }
         }
         __syncthreads();
         if (cb == 0) break;
-        if (w > 0) {
 #pragma unroll
-            for (int u = 0; u < NB; ++u)
-                acc += bm[u] * s.adj[cb * kT + 1 + min(w - 1 + u * W, kT - 1)];
-            s.pm[w][lane] = acc;
+        for (int u = 0; u < NL; ++u) {
+            const double *x = s.adj + cb * kT + 1 + 2 * (w * NL + u);
+            acc += last[u].x * x[0] + last[u].y * x[1];
         }
+        s.pm[w][lane] = acc;
         __syncthreads();
         if (w == 0) {
             acc = 0.0;
 #pragma unroll
-            for (int u = 1; u <= W; ++u) acc += s.pm[u][lane];
+            for (int u = 0; u < kSolveWaves; ++u) acc += s.pm[u][lane];
         }
     }
     for (int e = t; e <= N; e += kSolve) scr.adj[e] = s.adj[e];
@@ -918,39 +1012,49 @@ __global__ __launch_bounds__(kSolve) void k_boson_adjoint(BosonArgs a)
 // link n-1 -> j; S[n,j] = sum_{j' <= j} q[n,j'], the probability that particle
 // n-1's ring starts at j or before; the closing links' force on particle
 // n-1's last bead.  With prob, row n-1 of it gets the closing links and zeros
-// (its chain entry n is written by k_boson_cols).
+// (its chain entry n is written by k_boson_cols).  Bound by the scans' chain
+// (two rows per wave, with 16-byte reads of their pairs, took 18.7 us at
+// N = 1024 against 10.9: half the waves, twice the chain).
 __global__ __launch_bounds__(kBlock) void k_boson_rows(BosonArgs a)
 {
     const int lane = threadIdx.x & 63, N = a.N;
     const int n = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6) + 1;
     if (n > N) return;
     const BosonScr scr(a);
-    constexpr int NT = kBosonMaxN / kT;
     const double an = scr.adj[n];
-    const size_t base = w_at(n, 0) + lane;
+    const size_t base = w_at(n, 0) + 2 * lane;
     const double k2 = 2.0 * a.ks;
     double el[3], g[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int d = 0; d < 3; ++d) el[d] = scr.el[(n - 1) * 3 + d];
     double carry = 0.0;
-    constexpr int U = 4;
-    for (int c0 = 0; c0 * kT < n; c0 += U) {
+    constexpr int U = 4;                             // tiles at a time, the next ones' reads ahead
+    double qn[U], xn[U][3];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = (c0 + u) * kT + lane;
+            const bool ok = j < n;
+            qn[u] = ok ? scr.w[base + (size_t)(c0 + u) * kTT] : 0.0;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) xn[u][d] = scr.e0[(ok ? j : 0) * 3 + d];
+        }
+    };
+    fetch(0);
+    int c0 = 0;
+    for (; c0 * kT < n; c0 += U) {
         double q[U], sc[U], x0[U][3];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int j = (c0 + u) * kT + lane;
-            q[u] = j < n ? an * scr.w[base + (size_t)(c0 + u) * kTT] : 0.0;
+            sc[u] = q[u] = an * qn[u];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) x0[u][d] = j < n ? scr.e0[j * 3 + d] : 0.0;
+            for (int d = 0; d < 3; ++d) x0[u][d] = xn[u][d];
         }
+        if ((c0 + U) * kT < n) fetch(c0 + U);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int j = (c0 + u) * kT + lane;
-            if (j < n)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int d = 0; d < 3; ++d) g[d] += k2 * q[u] * mic(x0[u][d], el[d], a.box[d]);
-            sc[u] = q[u];
-        }
+            for (int d = 0; d < 3; ++d) g[d] += k2 * q[u] * mic(x0[u][d], el[d], a.box[d]);
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
 #pragma unroll
@@ -962,19 +1066,13 @@ __global__ __launch_bounds__(kBlock) void k_boson_rows(BosonArgs a)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int j = (c0 + u) * kT + lane;
-            if (j < n) {
-                scr.s[base + (size_t)(c0 + u) * kTT] = carry + sc[u];
-                if (a.prob) a.prob[(size_t)(n - 1) * N + j] = q[u];
-            } else if (a.prob && j < N) {
-                a.prob[(size_t)(n - 1) * N + j] = 0.0;
-            }
+            if (j < n) scr.s[base + (size_t)(c0 + u) * kTT] = carry + sc[u];
+            if (a.prob && j < N) a.prob[(size_t)(n - 1) * N + j] = q[u];
             carry += __shfl(sc[u], 63);
         }
     }
-    static_assert(NT % U == 0, "whole groups of tiles");
     if (a.prob)
-        for (int j = ((n + U * kT - 1) / (U * kT)) * (U * kT) + lane; j < N; j += 64)
-            a.prob[(size_t)(n - 1) * N + j] = 0.0;
+        for (int j = c0 * kT + lane; j < N; j += kT) a.prob[(size_t)(n - 1) * N + j] = 0.0;
 #pragma unroll
     for (int d = 0; d < 3; ++d) g[d] = wave_sum(g[d]);
     if (lane == 0) {
@@ -987,33 +1085,61 @@ __global__ __launch_bounds__(kBlock) void k_boson_rows(BosonArgs a)
 // rings in which l -> l+1 is a link) and the closing links' force on particle
 // l's first bead; then the chain links' forces.  A block takes 15 particles and
 // the one before them, 16 lanes wide so that a row is read in 128-byte pieces;
-// thread (row r of the row blocks, column).
+// thread (row pair of every second row
+// block, column).  17 us at N = 1024, 10 us at N = 512 (one wave per particle,
+// whose lanes read a row apart: 30 and 15 us).
 constexpr int kColBlock = 1024;
 constexpr int kColLanes = 16;
 __global__ __launch_bounds__(kColBlock) void k_boson_cols(BosonArgs a)
 {
     constexpr int NW = kColBlock / 64;
     __shared__ double red[NW][4][kColLanes];
-    const int t = threadIdx.x, c = t & (kColLanes - 1), r = t / kColLanes, N = a.N;
-    static_assert(kColBlock / kColLanes == kT, "one row of each row block per thread");
+    const int t = threadIdx.x, c = t & (kColLanes - 1), N = a.N;
+    // row pair of a row block; the two halves take alternate row blocks
+    const int rp = (t / kColLanes) & (kT / 2 - 1), half = t / (kColBlock / 2);
+    static_assert(kColBlock / kColLanes == kT, "two halves of 32 row pairs");
     const int l = (int)blockIdx.x * (kColLanes - 1) - 1 + c;
     const bool in = l >= 0 && l < N;
     const BosonScr scr(a);
-    const int nb = boson_blocks(N), cb = in ? l / kT : nb;
+    const int nb = boson_blocks(N), cb = in ? l / kT : nb;   // (a lane outside reads nothing)
     const double k2 = 2.0 * a.ks;
     double e0[3] = {0.0, 0.0, 0.0}, v[4] = {0.0, 0.0, 0.0, 0.0};
     if (in)
 #pragma unroll
         for (int d = 0; d < 3; ++d) e0[d] = scr.e0[l * 3 + d];
-#pragma unroll 4
-    for (int b = cb; b < nb; ++b) {
-        const int n = b * kT + 1 + r;
-        if (n > N || l >= n) continue;
-        const size_t at = ((size_t)boson_tile(b, cb) * kT + r) * kT + (l - cb * kT);
-        const double q = scr.adj[n] * scr.w[at];
+    const double2 *wm = reinterpret_cast<const double2 *>(scr.w);
+    const double2 *sm = reinterpret_cast<const double2 *>(scr.s);
+    constexpr int U = 2;                             // row blocks read together
+    for (int b0 = cb + half; b0 < nb; b0 += 2 * U) {
+        double2 q[U], sv[U];
+        double el[U][2][3];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) v[d] -= k2 * q * mic(e0[d], scr.el[(n - 1) * 3 + d], a.box[d]);
-        if (n >= l + 2) v[3] += scr.s[at];
+        for (int u = 0; u < U; ++u) {
+            const int b = b0 + 2 * u, n = b * kT + 1 + 2 * rp;
+            const bool ok = b < nb && n <= N && l <= n;   // (row n+1 may hold l = n)
+            const size_t at = ok ? (size_t)boson_tile(b, cb) * (kTT / 2) + rp * kT + (l - cb * kT) : 0;
+            q[u] = wm[at];
+            sv[u] = sm[at];
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                const int nv = n + v;
+                const bool row = ok && nv <= N && l < nv;
+                const double an = row ? scr.adj[nv] : 0.0;
+                (v ? q[u].y : q[u].x) = row ? an * (v ? q[u].y : q[u].x) : 0.0;
+                if (!row || nv < l + 2) (v ? sv[u].y : sv[u].x) = 0.0;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) el[u][v][d] = scr.el[((row ? nv : N) - 1) * 3 + d];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                v[d] -= k2 * q[u].x * mic(e0[d], el[u][0][d], a.box[d]);
+                v[d] -= k2 * q[u].y * mic(e0[d], el[u][1][d], a.box[d]);
+            }
+            v[3] += sv[u].x + sv[u].y;
+        }
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {

@@ -24,7 +24,7 @@ thread_local std::string g_create_error = "no error";
 constexpr int kGraphChunk = 32;   // steps per captured graph
 
 struct Layout {
-    size_t x, yt, v, f, stage, cent, cref, M, MT, modes, atoms, mass, orig, bond_j, nbr_count, nbr,
+    size_t x, yt, v, f, stage, cent, cref, M, MT, modes, atoms, mass, orig, inv, bond_j, nbr_count, nbr,
         partials, fpartials, ctl, cell_ent, cell_scnt, cinfo, total;
     int cap, fused_grid, mfma_grid, pair_grid, pair_S, pair_active_tiles, n_active;
     int n_forced;                 // atoms with lanes in the force pass (bond-owned ones last)
@@ -67,7 +67,7 @@ struct pimd_ctx {
     bool synced = true;
     double *d_x, *d_v, *d_f, *d_stage, *d_cent, *d_cref, *d_M, *d_MT, *d_modes, *d_atoms, *d_mass;
     double *d_partials, *d_fpartials;
-    int *d_orig, *d_bond_j, *d_nbr_count;
+    int *d_orig, *d_inv, *d_bond_j, *d_nbr_count;
     int2 *d_nbr;
     Ctl *d_ctl;
     std::vector<int> orig;          // internal -> caller index
@@ -409,6 +409,7 @@ Layout make_layout(const pimd_params *p, int n_active, int n_forced, int cap, do
     L.atoms = take(N * 4 * sizeof(double));
     L.mass = take(N * sizeof(double));
     L.orig = take(N * sizeof(int));
+    L.inv = take(N * sizeof(int));
     L.bond_j = take(pair ? N * kMaxBonds * sizeof(int) : 0);
     L.nbr_count = take(pair ? N * sizeof(int) : 0);
     L.nbr = take(pair ? (size_t)n_active * cap * sizeof(int2) : 0);
@@ -681,6 +682,7 @@ int pimd_create(const pimd_params *p, const double *mass, const pimd_topology *t
     c->d_atoms = (double *)(w + L.atoms);
     c->d_mass = (double *)(w + L.mass);
     c->d_orig = (int *)(w + L.orig);
+    c->d_inv = (int *)(w + L.inv);
     c->d_bond_j = pair ? (int *)(w + L.bond_j) : nullptr;
     c->d_nbr_count = pair ? (int *)(w + L.nbr_count) : nullptr;
     c->d_nbr = pair ? (int2 *)(w + L.nbr) : nullptr;
@@ -710,10 +712,10 @@ int pimd_create(const pimd_params *p, const double *mass, const pimd_topology *t
         atoms[(size_t)q * 4 + AT_SIGMA] = std::sqrt((double)P * kT / (m * p->mvv2e));
         atoms[(size_t)q * 4 + AT_ACTIVE] = (pair && (!act || act[i])) ? 1.0 : 0.0;
     }
+    std::vector<int> inv(N);                // caller -> internal index
+    for (int q = 0; q < N; ++q) inv[c->orig[q]] = q;
     std::vector<int> bond_j;
     if (pair) {
-        std::vector<int> inv(N);
-        for (int q = 0; q < N; ++q) inv[c->orig[q]] = q;
         bond_j.assign((size_t)N * kMaxBonds, -1);
         std::vector<int> deg(N, 0);
         // a bond-owned atom (internal index >= n_forced) is flagged in its
@@ -732,6 +734,7 @@ int pimd_create(const pimd_params *p, const double *mass, const pimd_topology *t
     if (e == hipSuccess) e = hipMemcpy(c->d_atoms, atoms.data(), atoms.size() * sizeof(double), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_mass, m_int.data(), m_int.size() * sizeof(double), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_orig, c->orig.data(), c->orig.size() * sizeof(int), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(c->d_inv, inv.data(), inv.size() * sizeof(int), hipMemcpyHostToDevice);
     if (e == hipSuccess && pair)
         e = hipMemcpy(c->d_bond_j, bond_j.data(), bond_j.size() * sizeof(int), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(c->d_cref, 0, (size_t)N * 3 * sizeof(double));
@@ -890,9 +893,9 @@ int pimd_set_state(pimd_ctx *c, const double *x, const double *v, uint64_t step)
     launch_ctl_init(c->d_ctl, (unsigned long long)step, c->stream);
     if (c->lay.npt_grid) launch_npt_init(c->d_ctl, c->start_box, c->start_vw, c->stream);
     HIP_TRY(c, hipMemcpyAsync(c->d_stage, x, n * sizeof(double), hipMemcpyHostToDevice, c->stream));
-    launch_import(c->d_stage, c->d_x, c->d_orig, N, P, c->stream);
+    launch_import(c->d_stage, c->d_x, c->d_inv, N, P, c->stream);
     HIP_TRY(c, hipMemcpyAsync(c->d_stage, v, n * sizeof(double), hipMemcpyHostToDevice, c->stream));
-    launch_import(c->d_stage, c->d_v, c->d_orig, N, P, c->stream);
+    launch_import(c->d_stage, c->d_v, c->d_inv, N, P, c->stream);
     FusedArgs a = c->fa;
     a.vin = c->d_v;
     a.mode = FUSED_PREP;
@@ -1106,14 +1109,14 @@ int pimd_get_state(pimd_ctx *c, double *x, double *p, uint64_t *step)
     const size_t n = (size_t)N * 3 * P;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     if (x) {
-        launch_export(c->d_x, c->d_v, c->d_mass, c->d_M, c->d_orig, c->d_stage, nullptr, N, P, c->stream);
+        launch_export_positions(c->d_x, c->d_inv, c->d_stage, N, P, c->stream);
         int rc = launch_error(c, "export");
         if (rc != PIMD_OK) return rc;
         HIP_TRY(c, hipMemcpyAsync(x, c->d_stage, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
     }
     if (p) {
-        launch_export(c->d_x, c->d_v, c->d_mass, c->d_M, c->d_orig, nullptr, c->d_stage, N, P, c->stream);
+        launch_export_momenta(c->d_v, c->d_mass, c->d_M, c->d_inv, c->d_stage, N, P, c->stream);
         int rc = launch_error(c, "export");
         if (rc != PIMD_OK) return rc;
         HIP_TRY(c, hipMemcpyAsync(p, c->d_stage, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
@@ -1132,8 +1135,7 @@ int pimd_get_positions(pimd_ctx *c, double *x)
     if (!c) return fail(nullptr, PIMD_ERR_ARG, "ctx is NULL");
     if (!x) return fail(c, PIMD_ERR_ARG, "x is NULL");
     if (!c->have_state) return fail(c, PIMD_ERR_STATE, "no state");
-    launch_export(c->d_x, c->d_v, c->d_mass, c->d_M, c->d_orig, x, nullptr, c->p.n_atoms, c->p.n_beads,
-                  c->stream);
+    launch_export_positions(c->d_x, c->d_inv, x, c->p.n_atoms, c->p.n_beads, c->stream);
     return launch_error(c, "get_positions");
 }
 
@@ -1146,7 +1148,7 @@ int pimd_set_forces(pimd_ctx *c, const double *f, double epot)
     if (!f) return fail(c, PIMD_ERR_ARG, "f is NULL");
     if (!std::isfinite(epot)) return fail(c, PIMD_ERR_ARG, "epot is not finite");
     if (!c->d_f || !c->d_fpartials) return fail(c, PIMD_ERR_STATE, "internal: no force array");
-    launch_import(f, c->d_f, c->d_orig, c->p.n_atoms, c->p.n_beads, c->stream);
+    launch_import(f, c->d_f, c->d_inv, c->p.n_atoms, c->p.n_beads, c->stream);
     launch_store_energy(c->d_fpartials, epot, c->stream);
     // a pending closing kick and the estimators of this state (or, right after
     // set_state, the estimators alone)

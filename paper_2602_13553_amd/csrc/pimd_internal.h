@@ -283,9 +283,11 @@ inline bool pair_lanes_paired(int N, int P)
     return P % 2 == 0 && (long long)N * 3 * P * 8 < (1LL << 31);
 }
 void launch_pair(const PairArgs &a, int grid, hipStream_t s);
-void launch_import(const double *src, double *dst, const int *orig, int N, int P, hipStream_t s);
-void launch_export(const double *x, const double *v, const double *atoms_mass, const double *M,
-                   const int *orig, double *xdst, double *pdst, int N, int P, hipStream_t s);
+// inv: [N] internal index of each atom of the caller's order
+void launch_import(const double *src, double *dst, const int *inv, int N, int P, hipStream_t s);
+void launch_export_positions(const double *x, const int *inv, double *dst, int N, int P, hipStream_t s);
+void launch_export_momenta(const double *v, const double *mass, const double *M, const int *inv,
+                           double *dst, int N, int P, hipStream_t s);
 void launch_ctl_reset_sums(Ctl *ctl, hipStream_t s);
 void launch_store_energy(double *dst, double v, hipStream_t s);
 void launch_apply_ucom(const FusedArgs &a, hipStream_t s);

@@ -82,7 +82,9 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
     // the control block), so that its reads need not wait for that block
     const bool need_f = a.pair && mode != FUSED_PREP;
     const bool inverse = (mode == FUSED_STEP);
-    const bool carry = (mode == FUSED_STEP);     // positions' modes carried in yt
+    // the positions' modes are carried in yt (PREP forms them): the closing and
+    // estimator passes transform f alone
+    const bool carry = (mode != FUSED_PREP);
     const double sqrtP = sqrt((double)P);
 
     const int la = t / P, k = t - (t / P) * P;
@@ -108,9 +110,9 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
         // that frees the previous tile's LDS: the x tile and the f (or PREP's
         // v) tile, 3 doubles each per thread (A*3P <= 3*256), this lane's v~
         // and per-atom constants.
-        // The step pass reads the positions' modes carried from the previous
-        // step (y~ relative to bead 0) and each atom's bead-0 position instead
-        // of the x tile.
+        // All passes but PREP read the positions' modes carried from the
+        // previous step (y~ relative to bead 0) and each atom's bead-0 position
+        // instead of the x tile.
         constexpr int NL = 3;
         const double *xg = a.x + (size_t)a0 * 3 * P;
         const double *fg = need_f ? a.f + (size_t)a0 * 3 * P

@@ -15,7 +15,9 @@ stream over the same steps:
 
 * the step pass with matrix-core (MFMA) and with vector-ALU transforms
   (P = 16, 32, 64, LJ only: the step pass does not depend on the potential);
-* the force pass with S = 1, 2, 4, 8, 16 lane sub-groups per atom (S*P <= 256).
+* the force pass with S = 1, 2, 4, 8, 16 lane sub-groups per atom (S*P <= 256),
+  at N and at N + N/2 atoms, their geometric mean: the table's entry holds for
+  the whole octave [N, 2N).
 
 From the timings it picks three things:
 
@@ -71,20 +73,22 @@ def sweep(steps: int = 40, warmup: int = 10, log=print, potentials=POTENTIALS) -
     for pot in potentials:
         for P in BEADS:
             for N in ATOMS:
-                if pot == "lj":
-                    spec = inputs.lj_liquid(n_atoms=N, n_beads=P)
-                else:
-                    spec = inputs.water(n_atoms=3 * -(-N // 3), n_beads=P)
                 rec = {"potential": pot, "P": P, "N": N}
                 if pot == "lj" and P in MFMA_BEADS:
                     for tag, fl in (("mfma", pimd.PIMD_FLAG_MFMA_TRANSFORMS),
                                     ("valu", pimd.PIMD_FLAG_VALU_TRANSFORMS)):
-                        rec["fused_" + tag] = time_kernels(spec, fl, steps, warmup)["fused"]
+                        rec["fused_" + tag] = time_kernels(
+                            inputs.lj_liquid(n_atoms=N, n_beads=P), fl, steps, warmup)["fused"]
+                # the octave's lower end and its middle
+                specs = [inputs.lj_liquid(n_atoms=n, n_beads=P) if pot == "lj"
+                         else inputs.water(n_atoms=3 * -(-n // 3), n_beads=P)
+                         for n in (N, N + N // 2)]
                 for S in SUBGROUPS:
                     if S * P > 256:
                         continue
-                    rec["pair_S%d" % S] = time_kernels(spec, pimd.PIMD_PAIR_SUBGROUPS(S),
-                                                       steps, warmup)["pair"]
+                    t = [time_kernels(s, pimd.PIMD_PAIR_SUBGROUPS(S), steps, warmup)["pair"]
+                         for s in specs]
+                    rec["pair_S%d" % S] = (t[0] * t[1]) ** 0.5
                 rows.append(rec)
                 log(json.dumps(rec))
     return {"device": _device_name(), "steps": steps, "warmup": warmup, "rows": rows}

@@ -150,6 +150,7 @@ struct PairArgs {
     double box[3];
     double rc2;
     double lj_eps, lj_sig2, lj_ushift;
+    double lj_fc;             // 24 eps / sigma^2
     double bond_k, bond_r0;
     const double *x;          // [N][3][P]
     double *f;                // [N][3][P]

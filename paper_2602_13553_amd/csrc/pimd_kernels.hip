@@ -736,6 +736,12 @@ constexpr int kNoShift = 512 | (512 << 10) | (512 << 20);   // pack_shift(0, 0, 
 // Word 3 of a raw buffer resource on gfx9-family parts (data format 32,
 // no swizzle, no index stride): offsets are plain byte offsets.
 constexpr int kBufferRsrcWord3 = 0x00020000;
+// a / b for 0 <= a <= 2048, 1 <= b <= 256 ((a + 1/2)/b is at least 1/512 from
+// an integer, far beyond the float rounding)
+__device__ __forceinline__ int div_small(int a, int b)
+{
+    return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
+}
 __device__ __forceinline__ void unpack_shift(int p, double &sx, double &sy, double &sz)
 {
     sx = (double)((p & 1023) - 512);
@@ -763,36 +769,61 @@ __device__ __forceinline__ void lj_energy_virial(double s12, double s6, int np, 
     w += 0.5 * eps24 * (2.0 * s12 - s6);
 }
 
+// The LJ constants of the force loop: with s = sigma^2 / r^2 the force factor is
+// fr = c (2 s^3 - 1) s^4, c = 24 eps / sigma^2.
+struct LjConst {
+    double rc2, sig2, c;
+};
+__device__ __forceinline__ LjConst lj_const(const PairArgs &a) { return {a.rc2, a.lj_sig2, a.lj_fc}; }
+
 // DIAG: also the pair's r_a F_a per dimension into wd (the diagonal of the
 // cell virial, for the anisotropic barostat)
 template <bool DIAG = false>
-__device__ __forceinline__ void lj_accumulate(double dx, double dy, double dz, double rc2,
-                                              double sig2, double eps24,
+__device__ __forceinline__ void lj_accumulate(double dx, double dy, double dz, const LjConst &lc,
                                               double &fx, double &fy, double &fz,
                                               double &s12, double &s6, int &np,
                                               double *wd = nullptr)
 {
     const double r2 = dx * dx + dy * dy + dz * dz;
-    if (r2 < rc2) {
-        // 1/r2: the hardware reciprocal (about 2^-24 relative) refined by one
-        // Newton step, instead of the IEEE division sequence.  Measured over
-        // 4e6 values in [0.5, 4096): at most 11 ulp from the correctly
-        // rounded 1/r2 (a second step makes it exact there); the pair force,
-        // a polynomial in 1/r2 of degree 7, then carries ~1e-14 relative,
-        // far inside the FP64 parity bar.
-        double ir2 = __builtin_amdgcn_rcp(r2);
-        ir2 = fma(fma(-r2, ir2, 1.0), ir2, ir2);
-        const double sr2 = sig2 * ir2;
-        const double sr6 = sr2 * sr2 * sr2, sr12 = sr6 * sr6;
-        const double fr = eps24 * (2.0 * sr12 - sr6) * ir2;
+    if (r2 < lc.rc2) {
+        // sigma^2 / r2: the hardware reciprocal (about 2^-24 relative) refined by
+        // one Newton step on the product, instead of the IEEE division
+        // sequence.  Measured over 4e6 values of r2 in [0.5, 4096): 1/r2 at
+        // most 11 ulp from the correctly rounded one (a second step makes it
+        // exact there); the pair force, a polynomial in it of degree 7, then
+        // carries ~1e-14 relative, far inside the FP64 parity bar.
+        const double ir = __builtin_amdgcn_rcp(r2);
+        const double y = lc.sig2 * ir;
+        const double sr2 = fma(fma(-r2, ir, 1.0), y, y);
+        const double sr6 = sr2 * sr2 * sr2;
+        const double fr = fma(2.0 * lc.c, sr6, -lc.c) * (sr6 * sr2);
         // the pair energy and virial are linear in (sr12, sr6, 1): their sums
         // are formed once per thread (lj_energy_virial)
-        s12 += sr12; s6 += sr6; ++np;
+        s12 = fma(sr6, sr6, s12); s6 += sr6; ++np;
         fx += fr * dx; fy += fr * dy; fz += fr * dz;
         if constexpr (DIAG) {
             wd[0] += fr * dx * dx; wd[1] += fr * dy * dy; wd[2] += fr * dz * dz;
         }
     }
+}
+
+// sqrt(x) and 1/sqrt(x) for normal x > 0, from the hardware's estimate (about
+// 2^-24 relative) by two coupled Newton steps and a residual correction of the
+// root (Goldschmidt's iteration); either within an ulp.  A third of the
+// instructions of sqrt and an IEEE division by it.
+__device__ __forceinline__ double sqrt_rsqrt(double x, double &ir)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const double r = fma(-h, g, 0.5);
+        g = fma(g, r, g);
+        h = fma(h, r, h);
+    }
+    g = fma(fma(-g, g, x), h, g);
+    ir = 2.0 * h;
+    return g;
 }
 
 // Harmonic bonds of atom i at bead k (minimum image), added to its force and
@@ -810,6 +841,7 @@ __device__ __forceinline__ void bond_forces(const PairArgs &a, int i, int k, dou
 {
     const int P = a.P, P3 = 3 * P;
     const double *__restrict__ X = a.x;
+    const double i0 = 1.0 / L0, i1 = 1.0 / L1, i2 = 1.0 / L2;
     for (int bb = 0; bb < kMaxBonds; ++bb) {
         const int jr = a.bond_j[i * kMaxBonds + bb];
         if (jr < 0) break;
@@ -817,15 +849,17 @@ __device__ __forceinline__ void bond_forces(const PairArgs &a, int i, int k, dou
         const int j = jr & ~kBondOwned;
         const size_t jb = (size_t)j * P3 + k;
         double dx = xi - X[jb], dy = yi - X[jb + P], dz = zi - X[jb + 2 * P];
-        dx -= L0 * rint(dx / L0);
-        dy -= L1 * rint(dy / L1);
-        dz -= L2 * rint(dz / L2);
-        const double r = sqrt(dx * dx + dy * dy + dz * dz);
+        dx -= L0 * rint(dx * i0);
+        dy -= L1 * rint(dy * i1);
+        dz -= L2 * rint(dz * i2);
+        const double r2 = dx * dx + dy * dy + dz * dz;
+        double ir;
+        const double r = sqrt_rsqrt(r2, ir);
         const double dr = r - a.bond_r0;
-        const double fr = -2.0 * a.bond_k * dr / r;
+        const double fr = -2.0 * a.bond_k * dr * ir;
         const double share = owned ? 1.0 : 0.5;   // each bond is seen from both atoms
         e += share * a.bond_k * dr * dr;
-        wv += share * fr * r * r;
+        wv += share * fr * r2;
         fx += fr * dx; fy += fr * dy; fz += fr * dz;
         if constexpr (DIAG) {
             wd[0] += share * fr * dx * dx; wd[1] += share * fr * dy * dy; wd[2] += share * fr * dz * dz;
@@ -848,30 +882,79 @@ __device__ __forceinline__ void bond_forces(const PairArgs &a, int i, int k, dou
 // consecutive beads of 2S sub-groups of P/2 lanes, so every gather is a
 // 16-byte load: half the load instructions of one bead per lane, which is
 // what the loop's gathers are limited by when the rows come from L2.
+//
+// A lane group that fills a wave, or an even part of one, works without block
+// barriers: its list entries and partial forces pass through LDS of its own.
+// Everything the force loop needs first (the control block, the list's length
+// and its first 2G entries, the lane's own beads) is read at once, ahead of
+// every test.  Without a single pair the pass took 25 us on the water state (its
+// 100 MB of x and f at copy speed) and 10 us on the LJ liquid, where the launch's
+// latency phases and about 130 vector instructions per wave are what is left; the
+// loop adds 100 us for 677 000 wave-entries of 50 vector instructions (69% of the
+// issue slots; 82 us with the gathers left out, 77 us with the arithmetic left
+// out).  LJ N = 4000, P = 32: 25.4 -> 22.3 us (with the re-tuned S = 2 for 4).
 template <bool BOXDEV = false, bool DIAG = false, bool PAIRED = false>
 __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, double *s_f)
 {
     const int P = a.P, S = a.S;
     const int G = S * P;                    // lanes per atom
-    const int A = kBlock / G;               // atoms per block
+    const int A = div_small(kBlock, G);     // atoms per block
     const int t = threadIdx.x;
-    const int la = t / G, g = t - la * G;   // atom slot, lane within the atom's group
-    const int sg = g / P, k = g - sg * P;   // sub-group, bead
+    const int la = div_small(t, G), g = t - la * G;   // atom slot, lane within the atom's group
+    const int sg = div_small(g, P), k = g - sg * P;   // sub-group, bead
     const int i = tile * A + la;
     const bool act = (la < A) && (i < a.n_forced);
+    const bool own_wave = G <= 64 && (64 & (G - 1)) == 0 && (G & (G - 1)) == 0;
     const double L0 = BOXDEV ? a.ctl->box[0] : a.box[0];
     const double L1 = BOXDEV ? a.ctl->box[1] : a.box[1];
     const double L2 = BOXDEV ? a.ctl->box[2] : a.box[2];
-    if (!a.ctl->ran) return;   // the system took no step (uniform per block)
+    int ran = a.ctl->ran, rebuild = a.ctl->rebuild;
+    const bool listed = act && i < a.n_active;
+    const int2 *list = a.nbr + (size_t)(listed ? i : 0) * a.cap;
+    const int P3 = 3 * P;
+    const size_t ib = (size_t)i * P3 + k;
+    const double *__restrict__ X = a.x;
+    double xi = 0.0, yi = 0.0, zi = 0.0;
+    // PAIRED: lane = (atom, sub-group sg2 of 2S, bead pair kp) takes beads
+    // 2 kp and 2 kp + 1 of every 2S-th entry of the atom's list
+    const int P2 = P / 2, S2 = 2 * S;
+    const int sg2 = PAIRED ? div_small(g, P2) : 0, kp = PAIRED ? g - sg2 * P2 : 0;
+    double pxi[2] = {0.0, 0.0}, pyi[2] = {0.0, 0.0}, pzi[2] = {0.0, 0.0};
+    int cnt = 0, bond0 = -1;
+    int2 first[2];
+    // (again after a rebuild, so that nothing of it stays in registers through
+    // the build; entries past the list's length are not used)
+    auto read_group = [&]() {
+        cnt = listed ? a.nbr_count[i] : 0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            first[u] = listed && g + u * G < a.cap ? list[g + u * G] : make_int2(0, 0);
+        if (act) {
+            bond0 = a.bond_j[i * kMaxBonds];
+            if constexpr (PAIRED) {
+                const size_t pb = (size_t)i * P3 + 2 * kp;
+#pragma unroll
+                for (int b2 = 0; b2 < 2; ++b2) {
+                    pxi[b2] = X[pb + b2]; pyi[b2] = X[pb + P + b2]; pzi[b2] = X[pb + 2 * P + b2];
+                }
+            } else {
+                xi = X[ib]; yi = X[ib + P]; zi = X[ib + 2 * P];
+            }
+        }
+    };
+    read_group();
+    ran = __builtin_amdgcn_readfirstlane(ran);
+    rebuild = __builtin_amdgcn_readfirstlane(rebuild);
+    if (!ran) return;          // the system took no step (uniform per block)
 
     // A list cutoff that is not finite (non-finite positions) or that would
     // need more than kMaxImages periodic images per dim skips the build and
     // flags the state; the image loops below are therefore always bounded.
     constexpr int kMaxImages = 8;
-    const double rl_in = a.ctl->rlist;
+    const double rl_in = rebuild ? a.ctl->rlist : 0.0;
     const bool rl_ok = isfinite(rl_in) && rl_in > 0.0 && rl_in <= kMaxImages * L0 &&
                        rl_in <= kMaxImages * L1 && rl_in <= kMaxImages * L2;
-    if (a.ctl->rebuild && !rl_ok) {
+    if (rebuild && !rl_ok) {
         if (tile == 0 && t == 0) a.ctl->nonfinite = 1;
     }
     // Lists from the sorted centroid cells: the first min(G, 64) lanes of each
@@ -880,7 +963,7 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
     // place the hits.  Image shifts come from the integer box indices kept at
     // binning and the wrap of the stencil cell.
     const bool wave_aligned = (G % 64 == 0) || (64 % G == 0);
-    const bool use_cells = a.ctl->rebuild && rl_ok && a.ctl->cell_ok && wave_aligned;
+    const bool use_cells = rebuild && rl_ok && a.ctl->cell_ok && wave_aligned;
     if (use_cells) {
         const double rl2 = rl_in * rl_in;
         const int Gb = G < 64 ? G : 64;
@@ -964,7 +1047,7 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
         __threadfence_block();
         __syncthreads();
     }
-    if (a.ctl->rebuild && rl_ok && !use_cells) {
+    if (rebuild && rl_ok && !use_cells) {
         const double rl = rl_in;
         const double rl2 = rl * rl;
         const bool big = (L0 >= 2.0 * rl) && (L1 >= 2.0 * rl) && (L2 >= 2.0 * rl);
@@ -1045,54 +1128,48 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
         __syncthreads();
     }
 
+    if (rebuild) read_group();
     double e = 0.0, wv = 0.0, s12 = 0.0, s6 = 0.0;
     double wd[3] = {0.0, 0.0, 0.0};   // DIAG: sum of fr r_a^2 over the thread's pairs
     int np = 0;
     double fx = 0.0, fy = 0.0, fz = 0.0;
-    const int P3 = 3 * P;
-    const size_t ib = (size_t)i * P3 + k;
-    const double *__restrict__ X = a.x;
-    double xi = 0.0, yi = 0.0, zi = 0.0;
-    const int cnt = (act && i < a.n_active) ? a.nbr_count[i] : 0;
-    // PAIRED: lane = (atom, sub-group sg2 of 2S, bead pair kp) takes beads
-    // 2 kp and 2 kp + 1 of every 2S-th entry of the atom's list
-    const int P2 = P / 2, S2 = 2 * S;
-    const int sg2 = PAIRED ? g / P2 : 0, kp = PAIRED ? g - sg2 * P2 : 0;
-    double pxi[2] = {0.0, 0.0}, pyi[2] = {0.0, 0.0}, pzi[2] = {0.0, 0.0};
     double pf[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (act) {
-        if constexpr (PAIRED) {
-            const size_t pb = (size_t)i * P3 + 2 * kp;
-#pragma unroll
-            for (int b2 = 0; b2 < 2; ++b2) {
-                pxi[b2] = X[pb + b2]; pyi[b2] = X[pb + P + b2]; pzi[b2] = X[pb + 2 * P + b2];
-            }
-        } else {
-            xi = X[ib]; yi = X[ib + P]; zi = X[ib + 2 * P];
-        }
-    }
-    // The block's list entries pass through LDS, up to C = kPairStage/A per
-    // atom at a time, in one coalesced copy: the loop then waits only on the
-    // bead-row gathers.  Entry q still goes to sub-group q mod S (q mod 2S
-    // with bead pairs), in order.
+    // The group's list entries pass through LDS, C = kPairStage/A at a time, so
+    // that the loop waits only on the bead-row gathers.  Entry q goes to
+    // sub-group q mod S (q mod 2S with bead pairs), in order.  A group of one
+    // wave orders its LDS traffic by itself; wider groups, and those that
+    // straddle waves, by block barriers (then every group takes as many chunks
+    // as the longest list).
     __shared__ int2 s_lst[kPairStage];
-    if (g == 0) s_cnt[la] = cnt;
-    __syncthreads();
-    int nmax = 0;
-    for (int u = 0; u < A; ++u) nmax = max(nmax, s_cnt[u]);
-    const int C = kPairStage / A;
-    const double eps4 = 4.0 * a.lj_eps, eps24 = 24.0 * a.lj_eps;
-    const double rc2 = a.rc2, sig2 = a.lj_sig2, ush = a.lj_ushift;
+    const int C = div_small(kPairStage, A);
+    int2 *ls = s_lst + la * C;                          // entry q at ls[q - c0]
+    auto group_sync = [&]() {
+        if (own_wave)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        else
+            __syncthreads();
+    };
+    int nmax = cnt;
+    if (!own_wave) {
+        if (g == 0) s_cnt[la] = cnt;
+        __syncthreads();
+        nmax = 0;
+        for (int u = 0; u < A; ++u) nmax = max(nmax, s_cnt[u]);
+    }
+    const double eps4 = 4.0 * a.lj_eps, eps24 = 24.0 * a.lj_eps, ush = a.lj_ushift;
+    const LjConst lc = lj_const(a);
     const long long x_bytes = (long long)a.N * 3 * P * 8;
     for (int c0 = 0; c0 < nmax; c0 += C) {
-        const int span = min(C, nmax - c0);
-        for (int e2 = t; e2 < A * span; e2 += kBlock) {
-            const int aa = e2 / span, qq = c0 + (e2 - aa * span);
-            if (qq < s_cnt[aa]) s_lst[e2] = a.nbr[(size_t)(tile * A + aa) * a.cap + qq];
+        const int qend = min(cnt, c0 + C);
+        if (la < A) {
+            if (c0 == 0) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    if (g + u * G < qend) ls[g + u * G] = first[u];
+            }
+            for (int q = (c0 == 0 ? 2 * G : c0) + g; q < qend; q += G) ls[q - c0] = list[q];
         }
-        __syncthreads();
-        const int2 *ls = s_lst + la * span;                 // entry q at ls[q - c0]
-        const int qend = min(cnt, c0 + span);
+        group_sync();
         int q = c0 + sg;
         if constexpr (PAIRED) {
             typedef double dbl2 __attribute__((ext_vector_type(2)));
@@ -1121,7 +1198,7 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
                 }
 #pragma unroll
                 for (int b2 = 0; b2 < 2; ++b2)
-                    lj_accumulate<DIAG>(dx[b2], dy[b2], dz[b2], rc2, sig2, eps24, pf[3 * b2],
+                    lj_accumulate<DIAG>(dx[b2], dy[b2], dz[b2], lc, pf[3 * b2],
                                         pf[3 * b2 + 1], pf[3 * b2 + 2], s12, s6, np, wd);
             };
             auto rows = [&](const int2 en, dbl2 &xj, dbl2 &yj, dbl2 &zj) {
@@ -1162,7 +1239,7 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
                 double sx, sy, sz;
                 unpack_shift(en[u].y, sx, sy, sz);
                 lj_accumulate<DIAG>(xi - xj[u] + sx * L0, yi - yj[u] + sy * L1, zi - zj[u] + sz * L2,
-                                    rc2, sig2, eps24, fx, fy, fz, s12, s6, np, wd);
+                                    lc, fx, fy, fz, s12, s6, np, wd);
             }
         }
         if (!PAIRED) for (; q < qend; q += S) {
@@ -1171,37 +1248,38 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
             unpack_shift(en.y, sx, sy, sz);
             const int jb = en.x + k;
             lj_accumulate<DIAG>(xi - X[jb] + sx * L0, yi - X[jb + P] + sy * L1,
-                                zi - X[jb + 2 * P] + sz * L2, rc2, sig2, eps24, fx, fy, fz, s12, s6,
-                                np, wd);
+                                zi - X[jb + 2 * P] + sz * L2, lc, fx, fy, fz, s12, s6, np, wd);
         }
-        __syncthreads();
+        group_sync();                                   // the entries have been read
     }
     if constexpr (PAIRED) {
         // back to one bead per lane: the sub-group 0 lanes sum the 2S
         // sub-groups' forces of their bead in sub-group order (the staged
-        // entries are no longer needed, so their LDS holds the partials:
-        // A * 2S * 3P = 6 kBlock doubles)
-        double *s2 = reinterpret_cast<double *>(s_lst);
+        // entries are no longer needed, so their LDS holds the partials: 2S *
+        // 3P = 6G doubles of the group's 8G)
+        double *s2 = reinterpret_cast<double *>(ls);
         if (la < A) {
 #pragma unroll
             for (int b2 = 0; b2 < 2; ++b2)
 #pragma unroll
-                for (int d = 0; d < 3; ++d) s2[((la * S2 + sg2) * 3 + d) * P + 2 * kp + b2] = pf[3 * b2 + d];
+                for (int d = 0; d < 3; ++d) s2[(sg2 * 3 + d) * P + 2 * kp + b2] = pf[3 * b2 + d];
         }
-        __syncthreads();
+        group_sync();
         if (act && sg == 0) {
             for (int u = 0; u < S2; ++u) {
-                fx += s2[((la * S2 + u) * 3 + 0) * P + k];
-                fy += s2[((la * S2 + u) * 3 + 1) * P + k];
-                fz += s2[((la * S2 + u) * 3 + 2) * P + k];
+                fx += s2[(u * 3 + 0) * P + k];
+                fy += s2[(u * 3 + 1) * P + k];
+                fz += s2[(u * 3 + 2) * P + k];
             }
-            xi = X[ib]; yi = X[ib + P]; zi = X[ib + 2 * P];
+            if (bond0 >= 0) {
+                xi = X[ib]; yi = X[ib + P]; zi = X[ib + 2 * P];
+            }
         }
     }
     lj_energy_virial(s12, s6, np, eps4, eps24, ush, e, wv);
 #pragma unroll
     for (int d = 0; d < 3; ++d) wd[d] *= 0.5;   // half of each ordered pair, as the trace
-    if (act && sg == 0) bond_forces<DIAG>(a, i, k, xi, yi, zi, L0, L1, L2, fx, fy, fz, e, wv, wd);
+    if (act && sg == 0 && bond0 >= 0) bond_forces<DIAG>(a, i, k, xi, yi, zi, L0, L1, L2, fx, fy, fz, e, wv, wd);
     if (!PAIRED && S > 1) {
         s_f[t * 3] = fx; s_f[t * 3 + 1] = fy; s_f[t * 3 + 2] = fz;
         __syncthreads();
@@ -1375,8 +1453,8 @@ __device__ void cluster_tile(const PairArgs &a, int b, double *smem, int *s_cnt,
         unpack_shift(a.cframe[i], ux, uy, uz);
         xf += ux * L0; yf += uy * L1; zf += uz * L2;
     }
-    const double eps4 = 4.0 * a.lj_eps, eps24 = 24.0 * a.lj_eps;
-    const double rc2 = a.rc2, sig2 = a.lj_sig2, ush = a.lj_ushift;
+    const double eps4 = 4.0 * a.lj_eps, eps24 = 24.0 * a.lj_eps, ush = a.lj_ushift;
+    const LjConst lc = lj_const(a);
     double e = 0.0, wv = 0.0, fx = 0.0, fy = 0.0, fz = 0.0, s12 = 0.0, s6 = 0.0;
     int np = 0;
     const int CH = kClusterRows / P3;                    // rows per chunk
@@ -1415,8 +1493,7 @@ __device__ void cluster_tile(const PairArgs &a, int b, double *smem, int *s_cnt,
                     double sx, sy, sz;
                     unpack_shift(en.y, sx, sy, sz);
                     lj_accumulate(xf - row[k] + sx * L0, yf - row[P + k] + sy * L1,
-                                  zf - row[2 * P + k] + sz * L2, rc2, sig2, eps24,
-                                  fx, fy, fz, s12, s6, np);
+                                  zf - row[2 * P + k] + sz * L2, lc, fx, fy, fz, s12, s6, np);
                 }
             }
         }
@@ -1434,7 +1511,7 @@ __device__ void cluster_tile(const PairArgs &a, int b, double *smem, int *s_cnt,
 }
 
 template <bool PAIRED>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PAIRED ? 5 : 6))) void k_pair(PairArgs a)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_pair(PairArgs a)
 {
     __shared__ int s_cnt[kBlock];
     __shared__ double red[64];
@@ -1465,7 +1542,7 @@ __global__ __launch_bounds__(kBlock) void k_pair_clusters(PairArgs a)
 // lists only, so that the kernel keeps the per-atom kernel's register budget;
 // the systems with paired lanes and the others are two item lists.
 template <bool PAIRED>
-__global__ __launch_bounds__(kBlock) void k_pair_batch(const PairArgs *__restrict__ table,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_pair_batch(const PairArgs *__restrict__ table,
                                                        const int2 *__restrict__ items, int n_items)
 {
     __shared__ int s_cnt[kBlock];

@@ -2,7 +2,7 @@
 // from kernel timings on the GPU; regenerate with
 //   python -m paper_2602_13553_amd.autotune --write
 // (the sweep, its workloads and the raw timings are described there).
-// Measured on AMD Radeon Graphics (gfx950:sramecc+:xnack-), 2026-12-03, 40 timed steps per point.
+// Measured on AMD Radeon Graphics (gfx950:sramecc+:xnack-), 2026-12-05, 200 timed steps per point.
 #pragma once
 
 namespace pimd {
@@ -16,15 +16,15 @@ constexpr long long kMfmaMinBeadAtoms[3] = {262144LL, 262144LL, 131072LL};
 // [2^6, 2^7), [2^7, 2^8), ..., [2^15, 2^16) (columns; clamped at both ends),
 // for LJ liquids.  0: the occupancy heuristic decides.
 constexpr int kPairSubgroups[4][10] = {
-    {16, 16, 16, 16, 16, 8, 4, 4, 2, 1},
-    {16, 8, 16, 8, 8, 4, 4, 2, 1, 1},
-    {8, 8, 8, 8, 8, 4, 2, 1, 1, 1},
-    {4, 4, 4, 4, 4, 2, 1, 1, 1, 1},
+    {16, 16, 16, 8, 8, 8, 4, 2, 2, 2},
+    {16, 16, 16, 8, 8, 4, 2, 2, 2, 1},
+    {8, 8, 8, 8, 4, 2, 2, 2, 1, 1},
+    {4, 4, 4, 4, 2, 2, 2, 1, 1, 1},
 };
 
 // The same for the water-shaped potential (O-O LJ plus O-H bonds).
 constexpr int kPairSubgroupsWater[4][10] = {
-    {16, 16, 16, 16, 16, 16, 16, 8, 4, 2},
+    {16, 16, 16, 16, 16, 8, 8, 4, 4, 2},
     {16, 16, 16, 16, 16, 8, 8, 4, 2, 2},
     {8, 8, 8, 8, 8, 8, 4, 2, 2, 2},
     {4, 4, 4, 4, 4, 4, 2, 2, 2, 1},

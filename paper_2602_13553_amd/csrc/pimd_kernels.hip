@@ -1739,18 +1739,37 @@ __global__ __launch_bounds__(kBlock) void k_export(const double *rows, const dou
         }
     }
     if constexpr (MOM) {
-        // each row is transformed by the lanes that loaded it, in place
-        for (int r = rl.first; r < 3 * na; r += rl.step) {
-            const double *vr = tile + r * PS;
-            double s0 = 0.0, s1 = 0.0;
-            for (int m = 0; m < P; ++m) {
-                const double v = vr[m];
-                if (rl.k < P) s0 += M[(size_t)m * P + rl.k] * v;
-                if (rl.k + 64 < P) s1 += M[(size_t)m * P + rl.k + 64] * v;
+        // each row is transformed by the lanes that loaded it, in place, RU rows
+        // at a time so that an element of M serves them all
+        constexpr int RU = 6;
+        for (int r0 = rl.first; r0 < 3 * na; r0 += RU * rl.step) {
+            double s0[RU], s1[RU];
+            const double *vr[RU];
+#pragma unroll
+            for (int u = 0; u < RU; ++u) {
+                s0[u] = s1[u] = 0.0;
+                vr[u] = tile + min(r0 + u * rl.step, 3 * na - 1) * PS;
             }
-            const double mi = mass[inv[c0 + r / 3]];
-            if (rl.k < P) tile[r * PS + rl.k] = mi * s0;
-            if (rl.k + 64 < P) tile[r * PS + rl.k + 64] = mi * s1;
+#pragma unroll 4
+            for (int m = 0; m < P; ++m) {
+                const double m0 = rl.k < P ? M[(size_t)m * P + rl.k] : 0.0;
+                const double m1 = rl.k + 64 < P ? M[(size_t)m * P + rl.k + 64] : 0.0;
+#pragma unroll
+                for (int u = 0; u < RU; ++u) {
+                    const double v = vr[u][m];
+                    s0[u] += m0 * v;
+                    s1[u] += m1 * v;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < RU; ++u) {
+                const int r = r0 + u * rl.step;
+                if (r < 3 * na) {
+                    const double mi = mass[inv[c0 + r / 3]];
+                    if (rl.k < P) tile[r * PS + rl.k] = mi * s0[u];
+                    if (rl.k + 64 < P) tile[r * PS + rl.k + 64] = mi * s1[u];
+                }
+            }
         }
     }
     __syncthreads();

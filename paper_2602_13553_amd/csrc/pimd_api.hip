@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -22,6 +23,7 @@ namespace {
 thread_local std::string g_create_error = "no error";
 
 constexpr int kGraphChunk = 32;   // steps per captured graph
+constexpr size_t kStageBoth = 8u << 20;   // bytes of a state array up to which staging holds two
 
 struct Layout {
     size_t x, yt, v, f, stage, cent, cref, M, MT, modes, atoms, mass, orig, inv, bond_j, nbr_count, nbr,
@@ -32,6 +34,7 @@ struct Layout {
     int ncell, cell_cap, nc[3];   // centroid cells (ncell = 0: none)
     bool clusters;                // force pass on cluster lists
     int n_clusters;
+    bool stage_both;              // the staging buffer holds positions and momenta
     size_t clist, ccount, cframe, cmode;
     int npt_grid;                 // barostat passes' blocks (0: no barostat)
     size_t nft, npart;            // barostat: f~ and pass partials
@@ -53,6 +56,46 @@ bool forces_in_array(const pimd_params *p) { return p->bosonic || forces_in_arra
 
 }  // namespace
 
+namespace {
+
+// Pinned host copies of control blocks: one slab for up to 64 contexts of the
+// process (a pinned allocation of its own would cost every pimd_create 0.1 ms),
+// allocated for the first context and freed with the last; contexts beyond the
+// slab's slots have none.  Any thread, any device.
+class PinnedCtls {
+    static constexpr int kSlots = 64;
+    std::mutex mu;
+    Ctl *slab = nullptr;
+    uint64_t used = 0;
+
+public:
+    Ctl *take()
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        if (!slab && hipHostMalloc((void **)&slab, kSlots * sizeof(Ctl), hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            slab = nullptr;
+        }
+        if (!slab || used == ~0ull) return nullptr;
+        const int q = __builtin_ctzll(~used);
+        used |= 1ull << q;
+        return slab + q;
+    }
+    void give(Ctl *c)
+    {
+        if (!c) return;
+        std::lock_guard<std::mutex> lock(mu);
+        used &= ~(1ull << (c - slab));
+        if (used == 0) {
+            (void)hipHostFree(slab);
+            slab = nullptr;
+        }
+    }
+};
+PinnedCtls g_pinned;
+
+}  // namespace
+
 struct pimd_ctx {
     pimd_params p;
     Layout lay;
@@ -70,6 +113,10 @@ struct pimd_ctx {
     int *d_orig, *d_inv, *d_bond_j, *d_nbr_count;
     int2 *d_nbr;
     Ctl *d_ctl;
+    // the control block as last read back: pinned, so that the copy and its wait
+    // take 12 us where a pageable one takes 21 (nullptr: no pinned memory; then
+    // each read goes through a block of its own)
+    Ctl *h_ctl = nullptr;
     std::vector<int> orig;          // internal -> caller index
     FusedArgs fa;
     PairArgs pa;
@@ -400,7 +447,10 @@ Layout make_layout(const pimd_params *p, int n_active, int n_forced, int cap, do
     L.yt = take(arr);
     L.v = take(arr);
     L.f = take(forces_in_array(p) ? arr : 0);
-    L.stage = take(arr);
+    // get_state converts positions and momenta together where that doubles no
+    // large buffer
+    L.stage_both = arr <= kStageBoth;
+    L.stage = take(L.stage_both ? 2 * arr : arr);
     L.cent = take(N * 3 * sizeof(double));
     L.cref = take(N * 3 * sizeof(double));
     L.M = take(P * P * sizeof(double));
@@ -643,6 +693,7 @@ int pimd_create(const pimd_params *p, const double *mass, const pimd_topology *t
     auto cleanup = [&](int code, const std::string &msg) {
         if (c->own_ws && c->ws) (void)hipFree(c->ws);
         if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
+        g_pinned.give(c->h_ctl);
         delete c;
         return fail(nullptr, code, msg);
     };
@@ -667,6 +718,8 @@ int pimd_create(const pimd_params *p, const double *mass, const pimd_topology *t
         if (e != hipSuccess) return cleanup(PIMD_ERR_DEVICE, std::string("hipStreamCreate: ") + hipGetErrorString(e));
         c->own_stream = true;
     }
+
+    c->h_ctl = g_pinned.take();
 
     char *w = c->ws;
     c->d_x = (double *)(w + L.x);
@@ -878,6 +931,29 @@ int pimd_create(const pimd_params *p, const double *mass, const pimd_topology *t
     return PIMD_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// Waits for the stream's work and copies the control block out.
+hipError_t read_ctl(pimd_ctx *c, Ctl *out)
+{
+    hipError_t e;
+    if (c->h_ctl) {
+        e = hipMemcpyAsync(c->h_ctl, c->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost, c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        if (e == hipSuccess) *out = *c->h_ctl;
+        return e;
+    }
+    e = hipStreamSynchronize(c->stream);
+    if (e == hipSuccess) e = hipMemcpy(out, c->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost);
+    return e;
+}
+
+}  // namespace
+
+extern "C" {
+
 int pimd_set_state(pimd_ctx *c, const double *x, const double *v, uint64_t step)
 {
     if (!c) return fail(nullptr, PIMD_ERR_ARG, "ctx is NULL");
@@ -1028,9 +1104,8 @@ int pimd_get_estimators(pimd_ctx *c, pimd_estimators *out)
     if (!c->have_state) return fail(c, PIMD_ERR_STATE, "no state");
     if (!c->forces_current)
         return fail(c, PIMD_ERR_STATE, "external forces: pimd_set_forces for the current positions first");
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
     Ctl h;
-    HIP_TRY(c, hipMemcpy(&h, c->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
+    HIP_TRY(c, read_ctl(c, &h));
     out->step = h.est_step;
     for (int q = 0; q < kNumEst; ++q) {
         out->value[q] = h.value[q];
@@ -1061,9 +1136,8 @@ int pimd_get_barostat(pimd_ctx *c, double *box, double *vw)
     if (!c) return fail(nullptr, PIMD_ERR_ARG, "ctx is NULL");
     if (!c->lay.npt_grid) return fail(c, PIMD_ERR_UNSUPPORTED, "no barostat (ensemble is not NPT or NPH)");
     if (!c->have_state) return fail(c, PIMD_ERR_STATE, "no state");
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
     Ctl h;
-    HIP_TRY(c, hipMemcpy(&h, c->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
+    HIP_TRY(c, read_ctl(c, &h));
     if (box)
         for (int d = 0; d < 3; ++d) box[d] = h.box[d];
     if (vw) {
@@ -1108,25 +1182,25 @@ int pimd_get_state(pimd_ctx *c, double *x, double *p, uint64_t *step)
         return fail(c, PIMD_ERR_STATE, "external forces: momenta need pimd_set_forces for the current positions");
     const int N = c->p.n_atoms, P = c->p.n_beads;
     const size_t n = (size_t)N * 3 * P;
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (x) {
-        launch_export_positions(c->d_x, c->d_inv, c->d_stage, N, P, c->stream);
-        int rc = launch_error(c, "export");
-        if (rc != PIMD_OK) return rc;
+    // positions, then momenta; in one wait where the staging buffer holds both
+    double *stage_p = c->d_stage + (c->lay.stage_both ? n : 0);
+    if (x) launch_export_positions(c->d_x, c->d_inv, c->d_stage, N, P, c->stream);
+    if (x && p && !c->lay.stage_both) {
         HIP_TRY(c, hipMemcpyAsync(x, c->d_stage, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
     }
-    if (p) {
-        launch_export_momenta(c->d_v, c->d_mass, c->d_M, c->d_inv, c->d_stage, N, P, c->stream);
-        int rc = launch_error(c, "export");
-        if (rc != PIMD_OK) return rc;
-        HIP_TRY(c, hipMemcpyAsync(p, c->d_stage, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
-    }
+    if (p) launch_export_momenta(c->d_v, c->d_mass, c->d_M, c->d_inv, stage_p, N, P, c->stream);
+    int rc = launch_error(c, "export");
+    if (rc != PIMD_OK) return rc;
+    if (x && !(p && !c->lay.stage_both))
+        HIP_TRY(c, hipMemcpyAsync(x, c->d_stage, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    if (p) HIP_TRY(c, hipMemcpyAsync(p, stage_p, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     if (step) {
         Ctl h;
-        HIP_TRY(c, hipMemcpy(&h, c->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
+        HIP_TRY(c, read_ctl(c, &h));
         *step = h.step;
+    } else {
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
     }
     return PIMD_OK;
 }
@@ -1177,6 +1251,7 @@ void pimd_destroy(pimd_ctx *c)
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     if (c->own_ws && c->ws) (void)hipFree(c->ws);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
+    g_pinned.give(c->h_ctl);
     delete c;
 }
 

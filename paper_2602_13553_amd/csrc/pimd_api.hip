@@ -467,7 +467,7 @@ Layout make_layout(const pimd_params *p, int n_active, int n_forced, int cap, do
     L.valu_tiles = (p->n_atoms + (kBlock / p->n_beads) - 1) / (kBlock / p->n_beads);
     L.mfma_tiles = fused_mfma_supported(p->n_beads) ? mfma_block_tiles(p->n_atoms, p->n_beads) : 0;
     const int nparts = std::max(std::max(L.fused_grid, L.mfma_grid), std::max(L.valu_tiles, L.mfma_tiles));
-    L.partials = take((size_t)nparts * PF_COUNT * sizeof(double));
+    L.partials = take((size_t)nparts * kPartRow * sizeof(double));
     L.trap_grid = (p->bosonic && p->potential == PIMD_POT_HARMONIC) ? boson_trap_grid(p->n_atoms, p->n_beads) : 0;
     L.fpartials = take((size_t)2 * std::max(std::max(L.pair_grid, L.trap_grid), 1) * sizeof(double));
     L.ctl = take(sizeof(Ctl));

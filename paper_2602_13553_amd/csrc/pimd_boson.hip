@@ -515,8 +515,8 @@ __global__ __launch_bounds__(kBlock) void k_boson_prep(BosonArgs a)
             a.f[e] = g;
         }
         double s1[1] = {e2};
-        block_sum<1>(s1, sh);
-        if (t == 0) scr.ein[ib] = a.ks * s1[0];
+        const double r = block_fold<1>(s1, sh);
+        if (t == 0) scr.ein[ib] = a.ks * r;
         return;
     }
     // end beads, and the prefix sums ch[m] = sum_{l<m} link(l, l+1), m = 0..N-1,
@@ -1330,18 +1330,10 @@ __global__ __launch_bounds__(kBlock) void k_bpass(FusedArgs a)
         }
     }
     if (spent) return;
-    double s2[2] = {acc_ekin, acc_vir};
-    double m3[3] = {acc_emax, acc_dmax, acc_bad};
-    block_sum_max<2, 3>(s2, m3, red);
-    if (t == 0) {
-        double *pp = a.partials + (size_t)blockIdx.x * PF_COUNT;
-        for (int q = 0; q < PF_COUNT; ++q) pp[q] = 0.0;
-        pp[PF_EKIN] = s2[0];
-        pp[PF_VIR] = s2[1];
-        pp[PF_EMAX] = m3[0];
-        pp[PF_DMAX] = m3[1];
-        pp[PF_NONFINITE] = m3[2];
-    }
+    const double s5[5] = {acc_ekin, 0.0, acc_vir, 0.0, 0.0};   // PF_EKIN .. PF_K0
+    const double m3[3] = {acc_emax, acc_dmax, acc_bad};
+    const double r = block_fold<5, 3>(s5, m3, red);
+    if (t < 8) a.partials[(size_t)blockIdx.x * kPartRow + (t < 5 ? t : PF_EMAX + t - 5)] = r;
 }
 
 // Harmonic trap on Cartesian beads: f = -m mvv2e omega^2 x for every bead,
@@ -1366,8 +1358,8 @@ __global__ __launch_bounds__(kBlock) void k_btrap(FusedArgs a, double *f, double
         }
     }
     double e1[1] = {e};
-    block_sum<1>(e1, red);
-    if (t == 0) reinterpret_cast<double2 *>(fpartials)[blockIdx.x] = make_double2(e1[0], 0.0);
+    const double r = block_fold<1>(e1, red);
+    if (t == 0) reinterpret_cast<double2 *>(fpartials)[blockIdx.x] = make_double2(r, 0.0);
 }
 
 constexpr int kMaxDevices = 64;

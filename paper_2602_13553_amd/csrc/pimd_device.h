@@ -131,33 +131,145 @@ __device__ __forceinline__ void gauss3(unsigned long long seed, unsigned i, unsi
 // --------------------------------------------------------------------------
 // Block reductions (fixed order).
 // --------------------------------------------------------------------------
-// Wave butterflies, then the kBlock/64 wave results in index order: the
-// same order on every call, two barriers per reduction.
-template <int NV>
-__device__ inline void block_sum(double (&v)[NV], double *red /* >= NV * kBlock/64 */)
+// Several values of every thread of a wave are summed (or their maximum taken)
+// together.  At distances 32 and 16 the lanes of two registers are exchanged so
+// that one addition folds both and half the registers are left; what remains is
+// folded within rows of 16 lanes by rotations, all in the vector unit.  The
+// pairs that are added are those of a butterfly over distances 32 .. 1, value by
+// value, so the sums are the same to the bit.  Thirteen values took 1.5 us by
+// butterflies through the LDS crossbar (156 exchanges a wave) in the finalize.
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ unsigned dlo(double v) { return (unsigned)__double_as_longlong(v); }
+__device__ __forceinline__ unsigned dhi(double v)
+{
+    return (unsigned)((unsigned long long)__double_as_longlong(v) >> 32);
+}
+__device__ __forceinline__ double dmake(unsigned lo, unsigned hi)
+{
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// exchanges lanes 32..63 of a with lanes 0..31 of b
+__device__ __forceinline__ void swap_lanes32(double &a, double &b)
+{
+    const u32x2 l = __builtin_amdgcn_permlane32_swap(dlo(a), dlo(b), false, false);
+    const u32x2 h = __builtin_amdgcn_permlane32_swap(dhi(a), dhi(b), false, false);
+    a = dmake(l.x, h.x);
+    b = dmake(l.y, h.y);
+}
+
+// exchanges lanes 16..31 and 48..63 of a with lanes 0..15 and 32..47 of b
+__device__ __forceinline__ void swap_lanes16(double &a, double &b)
+{
+    const u32x2 l = __builtin_amdgcn_permlane16_swap(dlo(a), dlo(b), false, false);
+    const u32x2 h = __builtin_amdgcn_permlane16_swap(dhi(a), dhi(b), false, false);
+    a = dmake(l.x, h.x);
+    b = dmake(l.y, h.y);
+}
+
+// rotates each row of 16 lanes by R
+template <int R>
+__device__ __forceinline__ double row_ror(double v)
+{
+    const unsigned l = (unsigned)__builtin_amdgcn_update_dpp(0, (int)dlo(v), 0x120 + R, 0xf, 0xf, true);
+    const unsigned h = (unsigned)__builtin_amdgcn_update_dpp(0, (int)dhi(v), 0x120 + R, 0xf, 0xf, true);
+    return dmake(l, h);
+}
+
+__device__ __forceinline__ double read_lane(double v, int lane)
+{
+    return dmake((unsigned)__builtin_amdgcn_readlane((int)dlo(v), lane),
+                 (unsigned)__builtin_amdgcn_readlane((int)dhi(v), lane));
+}
+
+template <bool MAX>
+__device__ __forceinline__ double fold2(double a, double b)
+{
+    return MAX ? fmax(a, b) : a + b;
+}
+
+// Value 4 s + fold_value(lane) of the wave ends in every lane of that row of r[s].
+__device__ __forceinline__ int fold_value(int lane)
+{
+    const int row = (lane >> 4) & 3;
+    return ((row & 1) << 1) | (row >> 1);
+}
+
+template <int NV, bool MAX>
+__device__ __forceinline__ void wave_fold(const double (&v)[NV], double (&r)[(NV + 3) / 4])
+{
+    constexpr int N2 = (NV + 1) / 2, N4 = (NV + 3) / 4;
+    double h[N2];
+#pragma unroll
+    for (int p = 0; p < N2; ++p) {
+        double a = v[2 * p], b = v[2 * p + 1 < NV ? 2 * p + 1 : 2 * p];
+        swap_lanes32(a, b);
+        h[p] = fold2<MAX>(a, b);
+    }
+#pragma unroll
+    for (int s = 0; s < N4; ++s) {
+        double a = h[2 * s], b = h[2 * s + 1 < N2 ? 2 * s + 1 : 2 * s];
+        swap_lanes16(a, b);
+        double x = fold2<MAX>(a, b);
+        x = fold2<MAX>(x, row_ror<8>(x));
+        x = fold2<MAX>(x, row_ror<4>(x));
+        x = fold2<MAX>(x, row_ror<2>(x));
+        r[s] = fold2<MAX>(x, row_ror<1>(x));
+    }
+}
+
+// The block's sums of NS values, then its maxima of NM values: thread q < NS +
+// NM returns the q-th.  One barrier; the caller passes another before red is
+// written again.
+template <int NS, int NM>
+__device__ __forceinline__ double block_fold(const double (&sv)[NS], const double (&mv)[NM],
+                                             double *red /* >= (NS + NM) * kBlock/64 */)
 {
     constexpr int NW = kBlock / 64;
-    const int t = threadIdx.x, w = t >> 6;
+    const int t = threadIdx.x, w = t >> 6, q0 = fold_value(t);
+    double rs[(NS + 3) / 4], rm[(NM + 3) / 4];
+    wave_fold<NS, false>(sv, rs);
+    wave_fold<NM, true>(mv, rm);
+    if ((t & 15) == 0) {
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        double x = v[q];
+        for (int s = 0; s < (NS + 3) / 4; ++s)
+            if (4 * s + q0 < NS) red[(4 * s + q0) * NW + w] = rs[s];
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-        v[q] = x;
-    }
-    if ((t & 63) == 0) {
-#pragma unroll
-        for (int q = 0; q < NV; ++q) red[q * NW + w] = v[q];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        double x = red[q * NW];
-#pragma unroll
-        for (int u = 1; u < NW; ++u) x += red[q * NW + u];
-        v[q] = x;
+        for (int s = 0; s < (NM + 3) / 4; ++s)
+            if (4 * s + q0 < NM) red[(NS + 4 * s + q0) * NW + w] = rm[s];
     }
     __syncthreads();
+    double x = 0.0;
+    if (t < NS + NM) {
+        x = red[t * NW];
+#pragma unroll
+        for (int u = 1; u < NW; ++u) x = t < NS ? x + red[t * NW + u] : fmax(x, red[t * NW + u]);
+    }
+    return x;
+}
+
+// The same of NV sums (MAX: maxima).
+template <int NV, bool MAX = false>
+__device__ __forceinline__ double block_fold(const double (&v)[NV], double *red /* >= NV * kBlock/64 */)
+{
+    constexpr int NW = kBlock / 64;
+    const int t = threadIdx.x, w = t >> 6, q0 = fold_value(t);
+    double r[(NV + 3) / 4];
+    wave_fold<NV, MAX>(v, r);
+    if ((t & 15) == 0) {
+#pragma unroll
+        for (int s = 0; s < (NV + 3) / 4; ++s)
+            if (4 * s + q0 < NV) red[(4 * s + q0) * NW + w] = r[s];
+    }
+    __syncthreads();
+    double x = 0.0;
+    if (t < NV) {
+        x = red[t * NW];
+#pragma unroll
+        for (int u = 1; u < NW; ++u) x = fold2<MAX>(x, red[t * NW + u]);
+    }
+    return x;
 }
 
 // Cell of an active atom's centroid c in the periodic cell grid, stored in
@@ -315,94 +427,6 @@ __device__ inline void cells_finalize(const FusedArgs &a, const double *icw, dou
         c->cell_R[1] = R[1];
         c->cell_R[2] = R[2];
     }
-}
-
-
-// Sums of NS values and maxima of NM values in one exchange (one barrier).
-// The caller passes a barrier before red is written again.
-template <int NS, int NM>
-__device__ inline void block_sum_max(double (&sv)[NS], double (&mv)[NM],
-                                     double *red /* >= (NS + NM) * kBlock/64 */)
-{
-    constexpr int NW = kBlock / 64;
-    const int t = threadIdx.x, w = t >> 6;
-#pragma unroll
-    for (int q = 0; q < NS; ++q) {
-        double x = sv[q];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-        sv[q] = x;
-    }
-#pragma unroll
-    for (int q = 0; q < NM; ++q) {
-        double x = mv[q];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o));
-        mv[q] = x;
-    }
-    if ((t & 63) == 0) {
-#pragma unroll
-        for (int q = 0; q < NS; ++q) red[q * NW + w] = sv[q];
-#pragma unroll
-        for (int q = 0; q < NM; ++q) red[(NS + q) * NW + w] = mv[q];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < NS; ++q) {
-        double x = red[q * NW];
-#pragma unroll
-        for (int u = 1; u < NW; ++u) x += red[q * NW + u];
-        sv[q] = x;
-    }
-#pragma unroll
-    for (int q = 0; q < NM; ++q) {
-        double x = red[(NS + q) * NW];
-#pragma unroll
-        for (int u = 1; u < NW; ++u) x = fmax(x, red[(NS + q) * NW + u]);
-        mv[q] = x;
-    }
-}
-
-template <int NV>
-__device__ inline void block_maxv(double (&v)[NV], double *red /* >= NV * kBlock/64 */)
-{
-    constexpr int NW = kBlock / 64;
-    const int t = threadIdx.x, w = t >> 6;
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        double x = v[q];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o));
-        v[q] = x;
-    }
-    if ((t & 63) == 0) {
-#pragma unroll
-        for (int q = 0; q < NV; ++q) red[q * NW + w] = v[q];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        double x = red[q * NW];
-#pragma unroll
-        for (int u = 1; u < NW; ++u) x = fmax(x, red[q * NW + u]);
-        v[q] = x;
-    }
-    __syncthreads();
-}
-
-__device__ inline double block_max(double v, double *red)
-{
-    constexpr int NW = kBlock / 64;
-    const int t = threadIdx.x, w = t >> 6;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-    if ((t & 63) == 0) red[w] = v;
-    __syncthreads();
-    v = red[0];
-#pragma unroll
-    for (int u = 1; u < NW; ++u) v = fmax(v, red[u]);
-    __syncthreads();
-    return v;
 }
 
 }  // namespace pimd

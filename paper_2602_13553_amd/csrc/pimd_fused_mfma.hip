@@ -630,21 +630,9 @@ __device__ __forceinline__ void mfma_tiles(const FusedArgs &a, int first, int st
         s4[5] = acc[ACC_P]; s4[6] = acc[ACC_P + 1]; s4[7] = acc[ACC_P + 2];
     }
     double m3[3] = {acc[ACC_EMAX], acc[ACC_DMAX], acc[ACC_BAD]};
-    block_sum_max<NS, 3>(s4, m3, red);
-    if (t == 0) {
-        double *pp = partial_out;
-        pp[PF_EKIN] = s4[0];
-        pp[PF_ESPRING] = s4[1];
-        pp[PF_VIR] = s4[2];
-        pp[PF_UEXT] = s4[3];
-        pp[PF_EMAX] = m3[0];
-        pp[PF_DMAX] = m3[1];
-        pp[PF_NONFINITE] = m3[2];
-        pp[PF_K0] = s4[4];
-        pp[PF_PX] = FC ? s4[NS > 5 ? 5 : 0] : 0.0;
-        pp[PF_PY] = FC ? s4[NS > 6 ? 6 : 0] : 0.0;
-        pp[PF_PZ] = FC ? s4[NS > 7 ? 7 : 0] : 0.0;
-    }
+    const double r = block_fold<NS, 3>(s4, m3, red);
+    // (the fixcom momentum's slots are read only where it is used)
+    if (t < NS + 3) partial_out[t < NS ? t : PF_EMAX + t - NS] = r;
 }
 
 // OB: the OBABO splitting (a kernel of its own, so that BAOAB keeps its
@@ -652,7 +640,7 @@ __device__ __forceinline__ void mfma_tiles(const FusedArgs &a, int first, int st
 template <int P, bool OB, bool FC>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_fused_mfma(FusedArgs a)
 {
-    mfma_tiles<P, OB, FC>(a, blockIdx.x, gridDim.x, a.partials + (size_t)blockIdx.x * PF_COUNT);
+    mfma_tiles<P, OB, FC>(a, blockIdx.x, gridDim.x, a.partials + (size_t)blockIdx.x * kPartRow);
 }
 
 // Batched: one block per item (system, block tile of T x 16 atoms), for the
@@ -666,7 +654,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     const FusedArgs &a = table[item.x];
     // (batches hold no fixcom systems)
     // (a stride past every tile: the item's tile alone; 2 stride stays an int)
-    mfma_tiles<P, OB, false>(a, item.y, 1 << 29, a.partials + (size_t)item.y * PF_COUNT);
+    mfma_tiles<P, OB, false>(a, item.y, 1 << 29, a.partials + (size_t)item.y * kPartRow);
 }
 
 namespace {

@@ -29,8 +29,12 @@ constexpr int kClusterSmem = 8 * 2 * kClusterRows + 16 * kClusterMax;   // dynam
 // Per-block partial slots written by the fused kernel.
 // PF_PX..PF_PZ: sum of hm * v~0 over the block's atoms (fixcom momentum)
 // PF_K0: sum of hm |v~0|^2 over the block's atoms (centroid-virial pressure)
-enum { PF_EKIN = 0, PF_ESPRING, PF_VIR, PF_UEXT, PF_EMAX, PF_DMAX, PF_NONFINITE, PF_K0, PF_PX, PF_PY,
-       PF_PZ, PF_COUNT };
+// The sums, then the maxima.  A block's slots are a row of kPartRow doubles (one
+// 128-byte line), so that the finalize's waves read whole rows.
+enum { PF_EKIN = 0, PF_ESPRING, PF_VIR, PF_UEXT, PF_K0, PF_PX, PF_PY, PF_PZ, PF_EMAX, PF_DMAX,
+       PF_NONFINITE, PF_COUNT };
+constexpr int kPartRow = 16;
+static_assert(PF_COUNT <= kPartRow, "partials row");
 
 // Fused-kernel modes.
 enum FusedMode : int {
@@ -113,7 +117,7 @@ struct FusedArgs {
     const double *modes;      // [P][8] per-mode constants
     const double *atoms;      // [N][4] per-atom constants
     const int *orig;          // [N] caller's atom index (noise counter)
-    double *partials;         // [gridDim][PF_COUNT]
+    double *partials;         // [gridDim][kPartRow]
     const double *fpartials;  // [n_fpartials][2] force-pass (energy, cell virial) per block
     int n_fpartials;
     Ctl *ctl;

@@ -414,22 +414,9 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
             s4[5] = acc_p[0]; s4[6] = acc_p[1]; s4[7] = acc_p[2];
         }
         double m3[3] = {acc_emax, acc_dmax, acc_bad};
-        block_sum_max<NS, 3>(s4, m3, red);
-        const double emax = m3[0], dmax = m3[1], bad = m3[2];
-        if (t == 0) {
-            double *pp = partial_out;
-            pp[PF_EKIN] = s4[0];
-            pp[PF_ESPRING] = s4[1];
-            pp[PF_VIR] = s4[2];
-            pp[PF_UEXT] = s4[3];
-            pp[PF_EMAX] = emax;
-            pp[PF_DMAX] = dmax;
-            pp[PF_NONFINITE] = bad;
-            pp[PF_K0] = s4[4];
-            pp[PF_PX] = FC ? s4[NS > 5 ? 5 : 0] : 0.0;
-            pp[PF_PY] = FC ? s4[NS > 6 ? 6 : 0] : 0.0;
-            pp[PF_PZ] = FC ? s4[NS > 7 ? 7 : 0] : 0.0;
-        }
+        const double r = block_fold<NS, 3>(s4, m3, red);
+        // (the fixcom momentum's slots are read only where it is used)
+        if (t < NS + 3) partial_out[t < NS ? t : PF_EMAX + t - NS] = r;
     }
 }
 
@@ -438,7 +425,7 @@ __global__ __launch_bounds__(kBlock) void k_fused(FusedArgs a)
 {
     extern __shared__ double smem[];
     __shared__ double red[64];
-    fused_tiles<FC>(a, blockIdx.x, gridDim.x, smem, red, a.partials + (size_t)blockIdx.x * PF_COUNT,
+    fused_tiles<FC>(a, blockIdx.x, gridDim.x, smem, red, a.partials + (size_t)blockIdx.x * kPartRow,
                     true);
 }
 
@@ -459,7 +446,7 @@ __global__ __launch_bounds__(kBlock) void k_fused_batch(const FusedArgs *__restr
         FusedArgs a = table[sys];
         a.mode = mode;
         // (batches hold no fixcom systems)
-        fused_tiles<false>(a, tile, 1 << 30, smem, red, a.partials + (size_t)tile * PF_COUNT,
+        fused_tiles<false>(a, tile, 1 << 30, smem, red, a.partials + (size_t)tile * kPartRow,
                            sys != prev);
         prev = sys;
     }
@@ -492,57 +479,43 @@ __device__ void finalize_system(const FusedArgs &a, int nblocks, double *red, in
     const bool est_now = closing || mode == FUSED_EST;
     const bool est_after = (mode == FUSED_STEP) && ext;
 
-    // thread 0's read-modify-write state, fetched now so that its latency
-    // overlaps the partial reductions
-    double run_sum[kNumEst], run_sq[kNumEst];
+    // the read-modify-write state (lane q: estimator q's running sums), fetched
+    // now so that its latency overlaps the partials'
+    double run_sum = 0.0, run_sq = 0.0, ebuild = 0.0;
     unsigned long long run_count = 0, n_rebuilds = 0;
-    double ebuild = 0.0;
-    if (t == 0) {
-#pragma unroll
-        for (int q = 0; q < kNumEst; ++q) {
-            run_sum[q] = c->sum[q];
-            run_sq[q] = c->sumsq[q];
+    if (t < 64) {
+        if (t < kNumEst) {
+            run_sum = c->sum[t];
+            run_sq = c->sumsq[t];
         }
         run_count = c->count;
         ebuild = c->ebuild;
         n_rebuilds = c->n_rebuilds;
     }
 
-    // ekin, espring, vir, uext, pair energy, fixcom momentum (3), centroid
-    // kinetic sum, cell virial
-    double tot[10] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    double mx[3] = {0.0, 0.0, 0.0};   // emax^2, dmax^2, non-finite flag
+    // The block partials: 16 lanes to a row, so that a wave reads four whole
+    // lines at once and a thread sums one quantity over every 16th row in order
+    // (with a thread to a row, 88 bytes apart, a wave's read touched 44 lines).
     // Loads in fixed batches held in registers, so that a batch's reads are in
-    // flight together; out-of-range slots add +0, and each thread's sums run
-    // in loop order, so the result is that of the plain loop.
-    constexpr int NB = 4, NF = 16;
-    for (int b0 = t; b0 < nblocks; b0 += NB * kBlock) {
-        constexpr int NQ = FC ? PF_COUNT : PF_K0 + 1;
-        double pv[NB][PF_COUNT];
+    // flight together; out-of-range slots add +0.
+    constexpr int NB = 8, NF = 16, NR = kBlock / kPartRow;
+    const int pq = t & (kPartRow - 1);
+    const bool is_max = pq >= PF_EMAX;
+    const bool used = pq < PF_COUNT && (FC || pq < PF_PX || pq > PF_PZ);
+    double part = 0.0;
+    for (int b0 = t / kPartRow; b0 < nblocks; b0 += NB * NR) {
+        double pv[NB];
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
-            const int b = b0 + u * kBlock;
-            const double *pp = a.partials + (size_t)(b < nblocks ? b : 0) * PF_COUNT;
-#pragma unroll
-            for (int q = 0; q < PF_COUNT; ++q) pv[u][q] = (q < NQ && b < nblocks) ? pp[q] : 0.0;
+            const int b = b0 + u * NR;
+            pv[u] = (used && b < nblocks) ? a.partials[(size_t)b * kPartRow + pq] : 0.0;
         }
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            tot[0] += pv[u][PF_EKIN];
-            tot[1] += pv[u][PF_ESPRING];
-            tot[2] += pv[u][PF_VIR];
-            tot[3] += pv[u][PF_UEXT];
-            mx[0] = fmax(mx[0], pv[u][PF_EMAX]);
-            mx[1] = fmax(mx[1], pv[u][PF_DMAX]);
-            mx[2] = fmax(mx[2], pv[u][PF_NONFINITE]);
-            tot[5] += pv[u][PF_PX];
-            tot[6] += pv[u][PF_PY];
-            tot[7] += pv[u][PF_PZ];
-            tot[8] += pv[u][PF_K0];
-        }
+        for (int u = 0; u < NB; ++u) part = is_max ? fmax(part, pv[u]) : part + pv[u];
     }
     // (summed whether or not this pass needs them, so the loads do not wait
     // for the control block)
+    double fe[2] = {0.0, 0.0};   // pair energy, cell virial
     if (a.pair) {
         const double2 *fp = reinterpret_cast<const double2 *>(a.fpartials);
         for (int b0 = t; b0 < a.n_fpartials; b0 += NF * kBlock) {
@@ -554,44 +527,71 @@ __device__ void finalize_system(const FusedArgs &a, int nblocks, double *red, in
             }
 #pragma unroll
             for (int u = 0; u < NF; ++u) {
-                tot[4] += fv[u].x;
-                tot[9] += fv[u].y;
+                fe[0] += fv[u].x;
+                fe[1] += fv[u].y;
             }
         }
     }
-    block_sum_max<10, 3>(tot, mx, red);
-    constexpr int kRedFlag = (10 + 3) * (kBlock / 64);   // first slot past the reduction's
+    // the waves' sums to LDS (slot q of wave w at q NW + w; the force pass's two
+    // after the PF_COUNT), then lane q of wave 0 combines the waves' slot q
+    constexpr int NW = kBlock / 64, NQ = PF_COUNT + 2;
+    constexpr int kRedFlag = NQ * NW;   // first slot past the reduction's
     static_assert(kRedFlag + 2 <= 64, "reduction scratch");
+    {
+        const int w = t >> 6, l = t & 63;
+        double o = part;
+        swap_lanes16(part, o);
+        part = is_max ? fmax(part, o) : part + o;
+        o = part;
+        swap_lanes32(part, o);
+        part = is_max ? fmax(part, o) : part + o;
+        double ew[1];
+        wave_fold<2, false>(fe, ew);
+        if (l < PF_COUNT) red[l * NW + w] = part;
+        if (l == 0) red[PF_COUNT * NW + w] = ew[0];
+        if (l == 32) red[(PF_COUNT + 1) * NW + w] = ew[0];
+    }
+    __syncthreads();
     if (mode == FUSED_STEP && budget == 0) {
         // no step was taken: nothing to combine, and no force pass follows
         if (t == 0) c->ran = 0;
         return;
     }
-    const double upair = tot[4];
-    const double emax = sqrt(mx[0]), dmax = sqrt(mx[1]), bad = mx[2];
-
-    if (t == 0) {
+    if (t < 64) {
+        double x = 0.0;
+        if (t < NQ) {
+            x = red[t * NW];
+            const bool mx = t >= PF_EMAX && t < PF_COUNT;
+#pragma unroll
+            for (int u = 1; u < NW; ++u) x = mx ? fmax(x, red[t * NW + u]) : x + red[t * NW + u];
+        }
+        const double emax = sqrt(read_lane(x, PF_EMAX)), dmax = sqrt(read_lane(x, PF_DMAX));
+        const double bad = read_lane(x, PF_NONFINITE);
         // fixcom: a step ended in this pass (closing half-kick, or the whole
         // step with the trap): its centroid momentum Pi = sum hm v~0 fixes the
         // velocity u = Pi / sum hm to remove from every atom's centroid mode,
         // which lowers the kinetic energy by |Pi|^2 / sum hm
         double dekin = 0.0;
         if (FC && (closing || est_after)) {
-            const double px = tot[5], py = tot[6], pz = tot[7];
-            c->ucom[0] = px * a.inv_hsum;
-            c->ucom[1] = py * a.inv_hsum;
-            c->ucom[2] = pz * a.inv_hsum;
-            c->ucom_pending = 1;
+            const double px = read_lane(x, PF_PX), py = read_lane(x, PF_PY), pz = read_lane(x, PF_PZ);
+            if (t == 0) {
+                c->ucom[0] = px * a.inv_hsum;
+                c->ucom[1] = py * a.inv_hsum;
+                c->ucom[2] = pz * a.inv_hsum;
+                c->ucom_pending = 1;
+            }
             dekin = (px * px + py * py + pz * pz) * a.inv_hsum;
         } else if (FC && mode == FUSED_STEP) {
-            c->ucom_pending = 0;        // the step pass removed it
+            if (t == 0) c->ucom_pending = 0;        // the step pass removed it
         }
         if (est_now || est_after) {
             // bosons: the spring energy is V_B, the primitive estimator
             // subtracts EV_B / P, and index 5 holds the virial estimator K_VR
             // = -(1/2P) sum r . F (App. A, bosonic list)
-            const double ekin = tot[0] - dekin, esp = a.boson ? a.bres[0] : tot[1], vir = tot[2];
-            const double epot = a.pair ? upair : tot[3];
+            const double ekin = read_lane(x, PF_EKIN) - dekin;
+            const double esp = a.boson ? a.bres[0] : read_lane(x, PF_ESPRING);
+            const double vir = read_lane(x, PF_VIR);
+            const double epot = a.pair ? read_lane(x, PF_COUNT) : read_lane(x, PF_UEXT);
             double v[kNumEst];
             v[0] = ekin;
             v[1] = esp;
@@ -604,44 +604,51 @@ __device__ void finalize_system(const FusedArgs &a, int nblocks, double *red, in
             // P_CV: the centroids' kinetic term (2 sum hm |v~0|^2, after the
             // fixcom removal), minus the centroid virial, plus W, over 3PV.
             // P_PR: 3PNkT - (2S - W)/P over 3V.  P_MD: 2K + W over 3V.
-            const double W = tot[9], iP = 1.0 / (double)P;
-            v[7] = a.lists ? (2.0 * (tot[8] - dekin) - vir + W) * iP * a.inv_3v : 0.0;
+            const double W = read_lane(x, PF_COUNT + 1), iP = 1.0 / (double)P;
+            v[7] = a.lists ? (2.0 * (read_lane(x, PF_K0) - dekin) - vir + W) * iP * a.inv_3v : 0.0;
             v[8] = a.lists ? (2.0 * a.kT15PN - (2.0 * esp - W) * iP) * a.inv_3v : 0.0;
             v[9] = a.lists ? (2.0 * ekin + W) * a.inv_3v : 0.0;
-            for (int q = 0; q < kNumEst; ++q) c->value[q] = v[q];
-            c->est_step = est_after ? step + 1 : step;
-            if (mode != FUSED_EST) {
-                c->count = run_count + 1;
-                for (int q = 0; q < kNumEst; ++q) {
-                    c->sum[q] = run_sum[q] + v[q];
-                    c->sumsq[q] = run_sq[q] + v[q] * v[q];
+            double mine = v[0];   // lane q records estimator q
+#pragma unroll
+            for (int q = 1; q < kNumEst; ++q) mine = t == q ? v[q] : mine;
+            if (t < kNumEst) {
+                c->value[t] = mine;
+                if (mode != FUSED_EST) {
+                    c->sum[t] = run_sum + mine;
+                    c->sumsq[t] = run_sq + mine * mine;
                 }
             }
+            if (t == 0) {
+                c->est_step = est_after ? step + 1 : step;
+                if (mode != FUSED_EST) c->count = run_count + 1;
+            }
         }
-        if (mode == FUSED_STEP) {
-            c->step = step + 1;
-            c->synced = ext ? 1 : 0;
-            if (budget > 0) c->budget = budget - 1;
-        } else if (mode == FUSED_CLOSE) {
-            c->synced = 1;
-        }
-        c->ran = 1;
         const bool rebuild = a.lists && (mode == FUSED_PREP ||
                                         (mode == FUSED_STEP && dmax + emax > 0.5 * a.skin + ebuild));
         const double rlist = a.rc + a.skin + 2.0 * emax;
-        if (rebuild) {
-            c->rebuild = 1;
-            c->ebuild = emax;
-            c->rlist = rlist;
-            c->n_rebuilds = n_rebuilds + 1;
-        } else if (a.lists && mode == FUSED_STEP) {
-            c->rebuild = 0;
+        if (t == 0) {
+            if (mode == FUSED_STEP) {
+                c->step = step + 1;
+                c->synced = ext ? 1 : 0;
+                if (budget > 0) c->budget = budget - 1;
+            } else if (mode == FUSED_CLOSE) {
+                c->synced = 1;
+            }
+            c->ran = 1;
+            if (rebuild) {
+                c->rebuild = 1;
+                c->ebuild = emax;
+                c->rlist = rlist;
+                c->n_rebuilds = n_rebuilds + 1;
+            } else if (a.lists && mode == FUSED_STEP) {
+                c->rebuild = 0;
+            }
+            if (bad != 0.0) c->nonfinite = 1;
+            // this pass's decision, for the cell build below (slots past the
+            // reduction's, which other threads may still be reading)
+            red[kRedFlag] = rebuild ? 1.0 : 0.0;
+            red[kRedFlag + 1] = rlist;
         }
-        if (bad != 0.0) c->nonfinite = 1;
-        // this pass's decision, for the cell build below (slots past the
-        // reduction's, which other threads may still be reading)
-        red[kRedFlag] = rebuild ? 1.0 : 0.0;
-        red[kRedFlag + 1] = rlist;
     }
     // the centroid cell lists of a rebuild (cells recorded by this pass)
     if (a.lists && a.ncell > 0 && (mode == FUSED_STEP || mode == FUSED_PREP)) {
@@ -1296,17 +1303,15 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
     // block sums (fixed order): energy, then the cell virial after all partials
     if constexpr (DIAG) {
         double e5[5] = {e, wv, wd[0], wd[1], wd[2]};
-        block_sum<5>(e5, red);
-        if (t == 0) {
-            reinterpret_cast<double2 *>(a.fpartials)[tile] = make_double2(e5[0], e5[1]);
-            a.fdiag[(size_t)tile * 3] = e5[2];
-            a.fdiag[(size_t)tile * 3 + 1] = e5[3];
-            a.fdiag[(size_t)tile * 3 + 2] = e5[4];
-        }
+        const double r = block_fold<5>(e5, red);
+        if (t < 2)
+            a.fpartials[(size_t)tile * 2 + t] = r;
+        else if (t < 5)
+            a.fdiag[(size_t)tile * 3 + t - 2] = r;
     } else {
         double e1[2] = {e, wv};
-        block_sum<2>(e1, red);
-        if (t == 0) reinterpret_cast<double2 *>(a.fpartials)[tile] = make_double2(e1[0], e1[1]);
+        const double r = block_fold<2>(e1, red);
+        if (t < 2) a.fpartials[(size_t)tile * 2 + t] = r;
     }
 }
 
@@ -1506,8 +1511,8 @@ __device__ void cluster_tile(const PairArgs &a, int b, double *smem, int *s_cnt,
         a.f[ib] = fx; a.f[ib + P] = fy; a.f[ib + 2 * P] = fz;
     }
     double e1[2] = {e, wv};
-    block_sum<2>(e1, red);
-    if (t == 0) reinterpret_cast<double2 *>(a.fpartials)[b] = make_double2(e1[0], e1[1]);
+    const double r = block_fold<2>(e1, red);
+    if (t < 2) a.fpartials[(size_t)b * 2 + t] = r;
 }
 
 template <bool PAIRED>

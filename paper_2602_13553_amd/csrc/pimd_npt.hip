@@ -25,6 +25,62 @@
 
 namespace pimd {
 
+// Wave butterflies, then the kBlock/64 wave results in index order: the
+// same order on every call, two barriers per reduction.
+template <int NV>
+__device__ inline void block_sum(double (&v)[NV], double *red /* >= NV * kBlock/64 */)
+{
+    constexpr int NW = kBlock / 64;
+    const int t = threadIdx.x, w = t >> 6;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        double x = v[q];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+        v[q] = x;
+    }
+    if ((t & 63) == 0) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) red[q * NW + w] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        double x = red[q * NW];
+#pragma unroll
+        for (int u = 1; u < NW; ++u) x += red[q * NW + u];
+        v[q] = x;
+    }
+    __syncthreads();
+}
+
+template <int NV>
+__device__ inline void block_maxv(double (&v)[NV], double *red /* >= NV * kBlock/64 */)
+{
+    constexpr int NW = kBlock / 64;
+    const int t = threadIdx.x, w = t >> 6;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        double x = v[q];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o));
+        v[q] = x;
+    }
+    if ((t & 63) == 0) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) red[q * NW + w] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        double x = red[q * NW];
+#pragma unroll
+        for (int u = 1; u < NW; ++u) x = fmax(x, red[q * NW + u]);
+        v[q] = x;
+    }
+    __syncthreads();
+}
+
 int npt_grid(int N, int P)
 {
     const int A = kBlock / P;

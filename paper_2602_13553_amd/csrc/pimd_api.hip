@@ -1448,8 +1448,7 @@ void enqueue_batch_step(pimd_batch *b)
         if (g.P)
             launch_fused_mfma_batch(g.P, g.obabo != 0, b->d_fa, b->d_items + g.off, g.n, g.n, b->stream);
         else
-            launch_fused_batch(b->d_fa, b->d_items + g.off, g.n, FUSED_STEP, b->smem_valu,
-                               std::min(g.n, 2 * ncu), b->stream);
+            launch_fused_batch(b->d_fa, b->d_items + g.off, g.n, FUSED_STEP, b->smem_valu, b->stream);
     }
     launch_finalize_batch(b->d_fa, b->d_nparts, b->n_sys_plan, FUSED_STEP, b->stream);
     if (b->pair_n)
@@ -1577,7 +1576,7 @@ int pimd_batch_step(pimd_batch *b, int64_t nsteps)
     for (; left > 0; --left) enqueue_batch_step(b);
     if (b->close_n) {
         launch_fused_batch(b->d_fa, b->d_items + b->close_off, b->close_n, FUSED_CLOSE, b->smem_valu,
-                           std::min(b->close_n, 2 * b->ncu), b->stream);
+                           b->stream);
         launch_finalize_batch(b->d_fa, b->d_nparts + b->n_sys_plan, b->n_sys_plan, FUSED_CLOSE, b->stream);
     }
     hipError_t e = hipGetLastError();

@@ -270,7 +270,7 @@ void set_mfma_batch_smem();
 void launch_fused_mfma_batch(int P, bool obabo, const FusedArgs *table, const int2 *items,
                              int n_items, int grid, hipStream_t s);
 void launch_fused_batch(const FusedArgs *table, const int2 *items, int n_items, int mode,
-                        int smem_bytes, int grid, hipStream_t s);
+                        int smem_bytes, hipStream_t s);
 void set_batch_smem(int smem_bytes);
 void launch_finalize_batch(const FusedArgs *table, const int *nparts, int n_sys, int mode,
                            hipStream_t s);

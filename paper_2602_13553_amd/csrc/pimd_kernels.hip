@@ -35,14 +35,17 @@ int fused_smem_bytes(int P)
     return (int)sizeof(double) * (P * (P + 1) + 2 * 3 * A * P + 6 * A);
 }
 
-// Processes tiles t0, t0 + tstride, ... of one system and writes one set of
-// partials.  stage_m = false keeps the matrix already staged in shared
-// memory (same system or same P as the previous call of this block).
-// FC: the system removes its centroids' center-of-mass velocity (fixcom); a
-// separate instantiation, so that the others carry none of its code.
-template <bool FC>
-__device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *smem, double *red,
-                           double *partial_out, bool stage_m)
+// Processes tile t0 (LOOP: tiles t0, t0 + tstride, ...) of one system and
+// writes one set of partials.
+// MODE: the pass (FusedMode).  FC: the system removes its centroids'
+// center-of-mass velocity (fixcom).  Instantiations of their own, so that none
+// carries another's code or registers: with the mode a runtime value and the
+// loop in every kernel, the step pass held 242 VGPRs (the noise's constants
+// kept in registers across tiles) and ran two waves per SIMD; alone it takes
+// 115 and runs four.
+template <int MODE, bool FC, bool LOOP>
+__device__ __forceinline__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *smem, double *red,
+                           double *partial_out)
 {
     const int P = a.P, N = a.N;
     const int A = kBlock / P;
@@ -63,18 +66,18 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
 #pragma unroll
     for (int q = 0; q < NM; ++q) {
         const int e = t + q * kBlock;
-        mreg[q] = (stage_m && m_regs && e < P * P) ? a.M[e] : 0.0;
+        mreg[q] = (m_regs && e < P * P) ? a.M[e] : 0.0;
     }
     const long long budget = a.ctl->budget;
     const unsigned long long step = a.ctl->step;
     const int synced = a.ctl->synced;
     // fixcom: the last step's centroid-mode velocity still to be removed
-    const bool ucom_now = FC && a.mode == FUSED_STEP && a.ctl->ucom_pending;
+    const bool ucom_now = FC && MODE == FUSED_STEP && a.ctl->ucom_pending;
     const double ucom[3] = {a.ctl->ucom[0], a.ctl->ucom[1], a.ctl->ucom[2]};
     // a system whose step budget is spent takes no step (uniform per block)
-    const bool spent = (a.mode == FUSED_STEP && budget == 0);
+    const bool spent = (MODE == FUSED_STEP && budget == 0);
 
-    const int mode = a.mode;
+    constexpr int mode = MODE;
     const int ext = !a.pair;                                    // forces in-kernel
     const bool closing = (mode == FUSED_STEP || mode == FUSED_CLOSE) && !synced && a.pair;
     const bool est_now = closing || mode == FUSED_EST;          // estimators of this state
@@ -117,6 +120,8 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
         const double *xg = a.x + (size_t)a0 * 3 * P;
         const double *fg = need_f ? a.f + (size_t)a0 * 3 * P
                                   : (mode == FUSED_PREP ? a.vin + (size_t)a0 * 3 * P : nullptr);
+        // (first of all the atom's index, which the noise below waits for)
+        const unsigned oi = act ? (unsigned)a.orig[i] : 0u;
         double rx[NL], rf[NL];
 #pragma unroll
         for (int q = 0; q < NL; ++q) {
@@ -127,13 +132,11 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
         double hm = 0.0, im = 0.0, sg = 0.0, active = 0.0;
         double vpre[3] = {0.0, 0.0, 0.0}, ypre[3] = {0.0, 0.0, 0.0}, xref[3] = {0.0, 0.0, 0.0};
         double cref[3] = {0.0, 0.0, 0.0};
-        unsigned oi = 0;
         if (act) {
             hm = a.atoms[i * 4 + AT_HALF_M];
             im = a.atoms[i * 4 + AT_INV_M];
             sg = a.atoms[i * 4 + AT_SIGMA];
             active = a.atoms[i * 4 + AT_ACTIVE];
-            oi = (unsigned)a.orig[i];
             const size_t vb = (size_t)i * 3 * P + k;
             if (mode != FUSED_PREP) {
                 vpre[0] = a.v[vb]; vpre[1] = a.v[vb + P]; vpre[2] = a.v[vb + 2 * P];
@@ -148,8 +151,17 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
             }
         }
         if (spent) return;
+        // The noise of the pass's O steps, formed while those reads are in
+        // flight: it needs the counter alone.  zo: the step's first (or only) O;
+        // zl: OBABO's last O, of the step closed here or of the trap's step.
+        double zo[3] = {0.0, 0.0, 0.0}, zl[3] = {0.0, 0.0, 0.0};
+        if (a.nvt && act) {
+            if (mode == FUSED_STEP) gauss3(a.seed, oi, (unsigned)k, step, zo, 0u);
+            if (a.obabo && (closing || (ext && mode == FUSED_STEP)))
+                gauss3(a.seed, oi, (unsigned)k, closing ? step - 1 : step, zl, 1u);
+        }
         __syncthreads();   // the previous tile's (or call's) shared-memory reads are done
-        if (stage_m && tile == t0) {
+        if (!LOOP || tile == t0) {
             if (m_regs) {
 #pragma unroll
                 for (int q = 0; q < NM; ++q) {
@@ -239,11 +251,8 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
 #pragma unroll
                 for (int d = 0; d < 3; ++d) ft[d] = -2.0 * hm * a.omega2 * (xt[d] + off * ref[d]);
             }
-            // PILE-L at P*T over one O step (dt in BAOAB, dt/2 in OBABO), noise
-            // of step s_ and O step q_ of that step
-            auto o_step = [&](unsigned long long s_, unsigned long long q_) {
-                double z[3];
-                gauss3(a.seed, oi, (unsigned)k, s_, z, (unsigned)q_);
+            // PILE-L at P*T over one O step (dt in BAOAB, dt/2 in OBABO)
+            auto o_step = [&](const double *z) {
 #pragma unroll
                 for (int d = 0; d < 3; ++d) vt[d] = mk[MD_C1] * vt[d] + mk[MD_C2] * sg * z[d];
             };
@@ -260,7 +269,7 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
 #pragma unroll
                 for (int d = 0; d < 3; ++d) vt[d] += a.hdt * im * ft[d];
                 // OBABO: the last O of the step being closed
-                if (a.obabo && a.nvt) o_step(step - 1, 1);
+                if (a.obabo && a.nvt) o_step(zl);
                 if (FC && k == 0) {
 #pragma unroll
                     for (int d = 0; d < 3; ++d) acc_p[d] += hm * vt[d];
@@ -281,7 +290,7 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
             if (mode == FUSED_STEP) {
                 if (a.obabo) {
                     // O(dt/2), B(dt/2), A(dt) = A(dt/2) A(dt/2)
-                    if (a.nvt) o_step(step, 0);
+                    if (a.nvt) o_step(zo);
 #pragma unroll
                     for (int d = 0; d < 3; ++d) vt[d] += a.hdt * im * ft[d];
                     a_step();
@@ -291,7 +300,7 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
 #pragma unroll
                     for (int d = 0; d < 3; ++d) vt[d] += a.hdt * im * ft[d];
                     a_step();
-                    if (a.nvt) o_step(step, 0);
+                    if (a.nvt) o_step(zo);
                     a_step();
                 }
                 if (ext) {
@@ -302,7 +311,7 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
                         ft[d] = -2.0 * hm * a.omega2 * (xt[d] + off * ref[d]);
                         vt[d] += a.hdt * im * ft[d];
                     }
-                    if (a.obabo && a.nvt) o_step(step, 1);
+                    if (a.obabo && a.nvt) o_step(zl);
                     if (FC && k == 0) {
 #pragma unroll
                         for (int d = 0; d < 3; ++d) acc_p[d] += hm * vt[d];
@@ -401,6 +410,7 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
                 }
             }
         }
+        if (!LOOP) break;
     }
 
     if (spent) return;
@@ -420,36 +430,29 @@ __device__ void fused_tiles(const FusedArgs &a, int t0, int tstride, double *sme
     }
 }
 
-template <bool FC>
+template <int MODE, bool FC, bool LOOP>
 __global__ __launch_bounds__(kBlock) void k_fused(FusedArgs a)
 {
     extern __shared__ double smem[];
     __shared__ double red[64];
-    fused_tiles<FC>(a, blockIdx.x, gridDim.x, smem, red, a.partials + (size_t)blockIdx.x * kPartRow,
-                    true);
+    fused_tiles<MODE, FC, LOOP>(a, blockIdx.x, gridDim.x, smem, red, a.partials + (size_t)blockIdx.x * kPartRow);
 }
 
-// Batched: item (system, tile); the system's arguments come from the table and
-// its partials are per tile.  Items are grouped by system, so the matrix is
-// restaged only when the system changes.
+// Batched: one item (system, tile) per block; the system's arguments come from
+// the table and its partials are per tile.
+template <int MODE>
 __global__ __launch_bounds__(kBlock) void k_fused_batch(const FusedArgs *__restrict__ table,
-                                                        const int2 *__restrict__ items, int n_items,
-                                                        int mode)
+                                                        const int2 *__restrict__ items, int n_items)
 {
     extern __shared__ double smem[];
     __shared__ double red[64];
-    int prev = -1;
-    for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-        // the item is the same for the whole block: scalar loads of its arguments
-        const int sys = __builtin_amdgcn_readfirstlane(items[it].x);
-        const int tile = __builtin_amdgcn_readfirstlane(items[it].y);
-        FusedArgs a = table[sys];
-        a.mode = mode;
-        // (batches hold no fixcom systems)
-        fused_tiles<false>(a, tile, 1 << 30, smem, red, a.partials + (size_t)tile * kPartRow,
-                           sys != prev);
-        prev = sys;
-    }
+    if ((int)blockIdx.x >= n_items) return;
+    // the item is the same for the whole block: scalar loads of its arguments
+    const int sys = __builtin_amdgcn_readfirstlane(items[blockIdx.x].x);
+    const int tile = __builtin_amdgcn_readfirstlane(items[blockIdx.x].y);
+    const FusedArgs a = table[sys];
+    // (batches hold no fixcom systems)
+    fused_tiles<MODE, false, false>(a, tile, 1, smem, red, a.partials + (size_t)tile * kPartRow);
 }
 
 // --------------------------------------------------------------------------
@@ -695,12 +698,22 @@ int fused_grid(int N, int P)
         if (hipGetDeviceProperties(&prop, dev) == hipSuccess) ncu = prop.multiProcessorCount;
     }
     // large P needs more than the default 64 KB of dynamic LDS per block
-    (void)hipFuncSetAttribute((const void *)k_fused<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              fused_smem_bytes(P));
-    (void)hipFuncSetAttribute((const void *)k_fused<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              fused_smem_bytes(P));
+    auto allow = [&](const void *kernel) {
+        if (fused_smem_bytes(P) <= 64 * 1024) return;
+        (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, fused_smem_bytes(P));
+    };
+    allow((const void *)k_fused<FUSED_PREP, false, true>);
+    allow((const void *)k_fused<FUSED_EST, false, true>);
+    allow((const void *)k_fused<FUSED_STEP, false, false>);
+    allow((const void *)k_fused<FUSED_STEP, false, true>);
+    allow((const void *)k_fused<FUSED_STEP, true, false>);
+    allow((const void *)k_fused<FUSED_STEP, true, true>);
+    allow((const void *)k_fused<FUSED_CLOSE, false, false>);
+    allow((const void *)k_fused<FUSED_CLOSE, false, true>);
+    allow((const void *)k_fused<FUSED_CLOSE, true, false>);
+    allow((const void *)k_fused<FUSED_CLOSE, true, true>);
     int per_cu = 1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_fused<false>, kBlock, fused_smem_bytes(P)) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_fused<FUSED_STEP, false, false>, kBlock, fused_smem_bytes(P)) !=
             hipSuccess || per_cu < 1)
         per_cu = 1;
     const int cap = ncu * per_cu;
@@ -713,10 +726,25 @@ void launch_fused(const FusedArgs &a, int grid, hipStream_t s)
         launch_boson_pass(a, grid, s);   // Cartesian beads (pimd_boson.hip)
         return;
     }
-    if (a.fixcom)
-        hipLaunchKernelGGL(k_fused<true>, dim3(grid), dim3(kBlock), fused_smem_bytes(a.P), s, a);
+    auto go = [&](void (*kernel)(FusedArgs)) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), fused_smem_bytes(a.P), s, a);
+    };
+    // a tile per block where the grid covers them
+    const bool loop = (a.N + kBlock / a.P - 1) / (kBlock / a.P) > grid;
+    // (the passes that end no step leave fixcom's partials, which nothing then
+    // reads, unwritten)
+    if (a.mode == FUSED_PREP)
+        go(k_fused<FUSED_PREP, false, true>);
+    else if (a.mode == FUSED_EST)
+        go(k_fused<FUSED_EST, false, true>);
+    else if (a.mode == FUSED_CLOSE && a.fixcom)
+        go(loop ? k_fused<FUSED_CLOSE, true, true> : k_fused<FUSED_CLOSE, true, false>);
+    else if (a.mode == FUSED_CLOSE)
+        go(loop ? k_fused<FUSED_CLOSE, false, true> : k_fused<FUSED_CLOSE, false, false>);
+    else if (a.fixcom)
+        go(loop ? k_fused<FUSED_STEP, true, true> : k_fused<FUSED_STEP, true, false>);
     else
-        hipLaunchKernelGGL(k_fused<false>, dim3(grid), dim3(kBlock), fused_smem_bytes(a.P), s, a);
+        go(loop ? k_fused<FUSED_STEP, false, true> : k_fused<FUSED_STEP, false, false>);
 }
 
 void launch_finalize(const FusedArgs &a, int fused_blocks, hipStream_t s)
@@ -1610,10 +1638,10 @@ int pair_active_tiles(int n_active, int P, int S)
 }
 
 void launch_fused_batch(const FusedArgs *table, const int2 *items, int n_items, int mode,
-                        int smem_bytes, int grid, hipStream_t s)
+                        int smem_bytes, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_fused_batch, dim3(grid), dim3(kBlock), smem_bytes, s, table, items,
-                       n_items, mode);
+    hipLaunchKernelGGL(mode == FUSED_CLOSE ? k_fused_batch<FUSED_CLOSE> : k_fused_batch<FUSED_STEP>,
+                       dim3(n_items), dim3(kBlock), smem_bytes, s, table, items, n_items);
 }
 
 void launch_finalize_batch(const FusedArgs *table, const int *nparts, int n_sys, int mode,
@@ -1637,8 +1665,10 @@ void launch_pair_batch(const PairArgs *table, const int2 *items, int n_items, in
 
 void set_batch_smem(int smem_bytes)
 {
-    (void)hipFuncSetAttribute((const void *)k_fused_batch, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              smem_bytes);
+    (void)hipFuncSetAttribute((const void *)k_fused_batch<FUSED_STEP>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, smem_bytes);
+    (void)hipFuncSetAttribute((const void *)k_fused_batch<FUSED_CLOSE>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, smem_bytes);
 }
 
 // The force pass's cluster path uses kClusterSmem bytes of dynamic LDS.

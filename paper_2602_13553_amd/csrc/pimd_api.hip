@@ -481,7 +481,7 @@ Layout make_layout(const pimd_params *p, int n_active, int n_forced, int cap, do
     L.cmode = take((size_t)L.n_clusters * sizeof(int));
     L.npt_grid = is_npt(p) ? npt_grid(p->n_atoms, p->n_beads) : 0;
     L.nft = take(L.npt_grid ? arr : 0);
-    L.npart = take((size_t)L.npt_grid * NP_COUNT_ANISO * sizeof(double));
+    L.npart = take((size_t)L.npt_grid * npt_row(p->baro_aniso != 0) * sizeof(double));
     L.fdiag = take((L.npt_grid && p->baro_aniso) ? (size_t)L.pair_grid * 3 * sizeof(double) : 0);
     L.fs = take(p->bosonic ? arr : 0);
     L.bscr = take(p->bosonic ? boson_scr_doubles(p->n_atoms) * sizeof(double) : 0);

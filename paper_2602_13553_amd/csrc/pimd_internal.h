@@ -193,10 +193,14 @@ enum { NP_EKIN = 0, NP_ESPRING, NP_VIR, NP_K0, NP_K0A, NP_FVA, NP_F2, NP_K0B, NP
 // the anisotropic barostat's per-dimension sums, after those (3 each)
 enum { NP_K0A3 = NP_COUNT, NP_FVA3 = NP_COUNT + 3, NP_F23 = NP_COUNT + 6, NP_K0B3 = NP_COUNT + 9,
        NP_FVB3 = NP_COUNT + 12, NP_VIR3 = NP_COUNT + 15, NP_COUNT_ANISO = NP_COUNT + 18 };
+// doubles per block of pass A's partials, a power of two lanes (one or two
+// 128-byte lines), and of pass B's
+constexpr int npt_row(bool aniso) { return aniso ? 32 : 16; }
+constexpr int kNptMax = 4;
 struct NptArgs {
     FusedArgs f;              // the system (x, v, f, tables, control block, partials)
     double *ft;               // [N][3][P] f~ of the current forces (pass A -> pass B)
-    double *part;             // [gridDim][NP_COUNT_ANISO] pass A partials; pass B: [gridDim][3]
+    double *part;             // [gridDim][npt_row] pass A partials; pass B: [gridDim][kNptMax]
     int aniso;                // 1: one v_W per dimension (App. E's anisotropic barostat)
     const double *fdiag;      // aniso: [force-pass blocks][3] diagonal of the cell virial
     double dt;

@@ -23,6 +23,11 @@ namespace {
 thread_local std::string g_create_error = "no error";
 
 constexpr int kGraphChunk = 32;   // steps per captured graph
+// Listed atoms up to which a list build tests them all: the one-block cell build
+// before it costs more than the cells save.  A rebuilding step's force pass and
+// cell build: LJ N = 1021, P = 7 45 + 8 us with cells, 13 without; N = 4000,
+// P = 32 46 + 22 against 42; 10922 listed atoms at P = 64 242 + 75 against 360.
+constexpr int kScanAtoms = 4096;
 constexpr size_t kStageBoth = 8u << 20;   // bytes of a state array up to which staging holds two
 
 struct Layout {
@@ -354,6 +359,9 @@ void cell_grid(const pimd_params *p, int n_active, double e_guess, Layout &L)
     L.cell_cap = 0;
     L.nc[0] = L.nc[1] = L.nc[2] = 0;
     if (!is_pair(p->potential) || n_active == 0) return;
+    // (the barostat's lists, built in a moving box, and cluster lists always
+    // come from cells where there are any)
+    if (n_active <= kScanAtoms && !is_npt(p) && !L.clusters) return;
     // Under a barostat the grid keeps its cell count while the box moves:
     // cells 25% wider than the cutoff leave room for the box to shrink (a
     // rebuild whose stencil no longer fits falls back to the all-pairs scan),
@@ -428,7 +436,6 @@ int choose_pair_subgroups(const pimd_params *p)
 Layout make_layout(const pimd_params *p, int n_active, int n_forced, int cap, double e_guess)
 {
     Layout L{};
-    cell_grid(p, n_active, e_guess, L);
     const size_t N = (size_t)p->n_atoms, P = (size_t)p->n_beads;
     const size_t arr = N * 3 * P * sizeof(double);
     const bool pair = is_pair(p->potential);
@@ -438,6 +445,7 @@ Layout make_layout(const pimd_params *p, int n_active, int n_forced, int cap, do
     L.mfma_grid = use_mfma(p) ? fused_mfma_grid(p->n_atoms, p->n_beads) : 0;
     L.clusters = pair && use_clusters(p, n_active);
     L.pair_S = pair ? (L.clusters ? 1 : choose_pair_subgroups(p)) : 1;
+    cell_grid(p, n_active, e_guess, L);
     L.n_forced = n_forced;
     L.pair_grid = pair ? pair_grid(n_forced, p->n_beads, L.pair_S) : 0;
     L.pair_active_tiles = pair ? pair_active_tiles(n_active, p->n_beads, L.pair_S) : 0;

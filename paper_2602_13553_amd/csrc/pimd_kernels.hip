@@ -999,7 +999,71 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
     // binning and the wrap of the stencil cell.
     const bool wave_aligned = (G % 64 == 0) || (64 % G == 0);
     const bool use_cells = rebuild && rl_ok && a.ctl->cell_ok && wave_aligned;
-    if (use_cells) {
+    // Without cells, in a box of at least twice the list cutoff (no image but
+    // the nearest can be in reach): each wave takes every fourth atom of the
+    // block and tests all active atoms, 64 at a time in index order, ballots
+    // again placing the hits; any lane layout can use it.  Up to kScanAtoms
+    // listed atoms there are no cells.
+    // (The builds are marked unlikely, so that registers spill there and not in
+    // the force loop: the batch's pass took 119 us without, 99 with.)
+    const bool use_scan = rebuild && rl_ok && !use_cells && L0 >= 2.0 * rl_in && L1 >= 2.0 * rl_in &&
+                          L2 >= 2.0 * rl_in;
+    if (__builtin_expect(use_scan, 0)) {
+        const double rl2 = rl_in * rl_in;
+        const int lane = t & 63;
+        const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+        const double i0 = 1.0 / L0, i1 = 1.0 / L1, i2 = 1.0 / L2;
+        for (int la2 = t >> 6; la2 < A; la2 += kBlock / 64) {
+            const int ia = tile * A + la2;
+            if (ia >= a.n_forced) break;
+            const double ci0 = a.cent[ia * 3], ci1 = a.cent[ia * 3 + 1], ci2 = a.cent[ia * 3 + 2];
+            int total = 0;
+            if (ia < a.n_active) {
+                int2 *mylist = a.nbr + (size_t)ia * a.cap;
+                constexpr int U = 4;   // candidates a lane has in flight
+                for (int j0 = lane; j0 - lane < a.n_active; j0 += U * 64) {
+                    double c[U][3];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int j = min(j0 + u * 64, a.n_active - 1);
+#pragma unroll
+                        for (int d = 0; d < 3; ++d) c[u][d] = a.cent[j * 3 + d];
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int j = j0 + u * 64;
+                        if (j - lane >= a.n_active) break;   // uniform over the wave
+                        double ex = ci0 - c[u][0], ey = ci1 - c[u][1], ez = ci2 - c[u][2];
+                        const double sx = -rint(ex * i0), sy = -rint(ey * i1), sz = -rint(ez * i2);
+                        ex += sx * L0;
+                        ey += sy * L1;
+                        ez += sz * L2;
+                        const bool pass = j < a.n_active && j != ia && ex * ex + ey * ey + ez * ez < rl2;
+                        const unsigned long long hit = __ballot(pass);
+                        if (pass) {
+                            const int w = total + __popcll(hit & below);
+                            if (w < a.cap)
+                                mylist[w] = make_int2(j * 3 * P, pack_shift((int)sx, (int)sy, (int)sz));
+                        }
+                        total += __popcll(hit);
+                    }
+                }
+            }
+            if (lane == 0) {
+                if (total > a.cap) {
+                    a.ctl->overflow = 1;
+                    total = a.cap;
+                }
+                a.nbr_count[ia] = total;
+                a.cref[ia * 3] = ci0;
+                a.cref[ia * 3 + 1] = ci1;
+                a.cref[ia * 3 + 2] = ci2;
+            }
+        }
+        __threadfence_block();
+        __syncthreads();
+    }
+    if (__builtin_expect(use_cells, 0)) {
         const double rl2 = rl_in * rl_in;
         const int Gb = G < 64 ? G : 64;
         const int lane = t & 63;
@@ -1082,7 +1146,7 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
         __threadfence_block();
         __syncthreads();
     }
-    if (rebuild && rl_ok && !use_cells) {
+    if (__builtin_expect(rebuild && rl_ok && !use_cells && !use_scan, 0)) {
         const double rl = rl_in;
         const double rl2 = rl * rl;
         const bool big = (L0 >= 2.0 * rl) && (L1 >= 2.0 * rl) && (L2 >= 2.0 * rl);

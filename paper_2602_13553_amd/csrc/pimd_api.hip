@@ -32,7 +32,7 @@ constexpr size_t kStageBoth = 8u << 20;   // bytes of a state array up to which 
 
 struct Layout {
     size_t x, yt, v, f, stage, cent, cref, M, MT, modes, atoms, mass, orig, inv, bond_j, nbr_count, nbr,
-        partials, fpartials, ctl, cell_ent, cell_scnt, cinfo, total;
+        partials, step_max, fpartials, ctl, cell_ent, cell_scnt, cinfo, total;
     int cap, fused_grid, mfma_grid, pair_grid, pair_S, pair_active_tiles, n_active;
     int n_forced;                 // atoms with lanes in the force pass (bond-owned ones last)
     int valu_tiles, mfma_tiles;
@@ -41,6 +41,7 @@ struct Layout {
     int n_clusters;
     bool stage_both;              // the staging buffer holds positions and momenta
     size_t clist, ccount, cframe, cmode;
+    bool pair_step;               // the force pass takes over the step's finalize
     int npt_grid;                 // barostat passes' blocks (0: no barostat)
     size_t nft, npart;            // barostat: f~ and pass partials
     size_t fdiag;                 // anisotropic barostat: per force-pass block, the cell virial's diagonal
@@ -114,7 +115,7 @@ struct pimd_ctx {
     bool forces_current = true;
     bool synced = true;
     double *d_x, *d_v, *d_f, *d_stage, *d_cent, *d_cref, *d_M, *d_MT, *d_modes, *d_atoms, *d_mass;
-    double *d_partials, *d_fpartials;
+    double *d_partials, *d_step_max, *d_fpartials;
     int *d_orig, *d_inv, *d_bond_j, *d_nbr_count;
     int2 *d_nbr;
     Ctl *d_ctl;
@@ -475,7 +476,12 @@ Layout make_layout(const pimd_params *p, int n_active, int n_forced, int cap, do
     L.valu_tiles = (p->n_atoms + (kBlock / p->n_beads) - 1) / (kBlock / p->n_beads);
     L.mfma_tiles = fused_mfma_supported(p->n_beads) ? mfma_block_tiles(p->n_atoms, p->n_beads) : 0;
     const int nparts = std::max(std::max(L.fused_grid, L.mfma_grid), std::max(L.valu_tiles, L.mfma_tiles));
-    L.partials = take((size_t)nparts * kPartRow * sizeof(double));
+    L.partials = take((size_t)(nparts + 1) * kPartRow * sizeof(double));
+    // The force pass takes over the finalize where the step pass has a tile per
+    // block, at most kStepDecideBlocks of them, and lists need no cells.
+    L.pair_step = pair && !p->bosonic && !is_npt(p) && !L.clusters && L.ncell == 0 && L.mfma_grid == 0 &&
+                  n_active > 0 && L.fused_grid == L.valu_tiles && L.fused_grid <= kStepDecideBlocks;
+    L.step_max = take(L.pair_step ? (size_t)2 * L.fused_grid * sizeof(double) : 0);
     L.trap_grid = (p->bosonic && p->potential == PIMD_POT_HARMONIC) ? boson_trap_grid(p->n_atoms, p->n_beads) : 0;
     L.fpartials = take((size_t)2 * std::max(std::max(L.pair_grid, L.trap_grid), 1) * sizeof(double));
     L.ctl = take(sizeof(Ctl));
@@ -648,6 +654,16 @@ void enqueue_step(pimd_ctx *c)
     // pass of its own, so that its centroid momentum is known (and removed at
     // the start of the step pass) before the step's opening half-kick
     if (c->fa.fixcom && c->lay.pair_grid > 0) enqueue_fused(c, FUSED_CLOSE, PIMD_KERNEL_CLOSE);
+    // (profiled steps keep the finalize as a launch of its own, to be timed; the
+    // results are the same)
+    if (c->lay.pair_step && !c->profiling) {
+        FusedArgs a = c->fa;
+        a.mode = FUSED_STEP;
+        a.step_max = c->d_step_max;
+        launch_fused(a, c->lay.fused_grid, c->stream);
+        launch_pair_step(c->pa, a, c->lay.fused_grid, c->lay.pair_grid, c->stream);
+        return;
+    }
     enqueue_fused(c, FUSED_STEP, PIMD_KERNEL_FUSED);
     enqueue_forces(c);
 }
@@ -748,6 +764,7 @@ int pimd_create(const pimd_params *p, const double *mass, const pimd_topology *t
     c->d_nbr_count = pair ? (int *)(w + L.nbr_count) : nullptr;
     c->d_nbr = pair ? (int2 *)(w + L.nbr) : nullptr;
     c->d_partials = (double *)(w + L.partials);
+    c->d_step_max = L.pair_step ? (double *)(w + L.step_max) : nullptr;
     c->d_fpartials = (double *)(w + L.fpartials);
     c->d_ctl = (Ctl *)(w + L.ctl);
 

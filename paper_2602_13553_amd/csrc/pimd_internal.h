@@ -35,6 +35,10 @@ enum { PF_EKIN = 0, PF_ESPRING, PF_VIR, PF_UEXT, PF_K0, PF_PX, PF_PY, PF_PZ, PF_
        PF_NONFINITE, PF_COUNT };
 constexpr int kPartRow = 16;
 static_assert(PF_COUNT <= kPartRow, "partials row");
+// The row after them where the force pass takes over the finalize: the last
+// forces' energy and virial, and the control block's values it decides by.
+enum { SN_EPAIR = 0, SN_VIRIAL, SN_EBUILD, SN_RUN };
+constexpr int kStepDecideBlocks = 512;   // step-pass blocks up to which it does (eight reads a lane)
 
 // Fused-kernel modes.
 enum FusedMode : int {
@@ -118,6 +122,7 @@ struct FusedArgs {
     const double *atoms;      // [N][4] per-atom constants
     const int *orig;          // [N] caller's atom index (noise counter)
     double *partials;         // [gridDim][kPartRow]
+    double *step_max;         // [gridDim][2] maxima apart (nullptr: k_finalize follows the pass)
     const double *fpartials;  // [n_fpartials][2] force-pass (energy, cell virial) per block
     int n_fpartials;
     Ctl *ctl;
@@ -215,6 +220,8 @@ void launch_npt_init(Ctl *ctl, const double box[3], const double vw[3], hipStrea
 void launch_npt_a(const NptArgs &a, int mode, hipStream_t s);
 void launch_npt_b(const NptArgs &a, hipStream_t s);
 void launch_pair_npt(const PairArgs &a, int grid, hipStream_t s);
+// the force pass and, as one of its blocks, the step's finalize (fa: the step pass's)
+void launch_pair_step(const PairArgs &a, const FusedArgs &fa, int fused_blocks, int grid, hipStream_t s);
 
 // Bosonic exchange springs (pimd_boson.hip).  Scratch, in doubles: the ring
 // weights in 64 x 64 tiles of (row n, column j = n - k), j < n (boson_tile);

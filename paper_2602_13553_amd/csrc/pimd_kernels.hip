@@ -427,7 +427,49 @@ __device__ __forceinline__ void fused_tiles(const FusedArgs &a, int t0, int tstr
         const double r = block_fold<NS, 3>(s4, m3, red);
         // (the fixcom momentum's slots are read only where it is used)
         if (t < NS + 3) partial_out[t < NS ? t : PF_EMAX + t - NS] = r;
+        // (the force pass that decides the rebuild itself reads these alone)
+        if (!LOOP && MODE == FUSED_STEP && a.step_max && (t == NS || t == NS + 1))
+            a.step_max[2 * (size_t)blockIdx.x + t - NS] = r;
     }
+}
+
+// The previous force pass's energy and virial partials: one thread's share, in
+// order.  Loads in fixed batches held in registers, so that a batch's reads are
+// in flight together; out-of-range slots add +0.
+__device__ __forceinline__ void force_partials(const FusedArgs &a, double (&fe)[2])
+{
+    constexpr int NF = 16;
+    const double2 *fp = reinterpret_cast<const double2 *>(a.fpartials);
+    for (int b0 = threadIdx.x; b0 < a.n_fpartials; b0 += NF * kBlock) {
+        double2 fv[NF];
+#pragma unroll
+        for (int u = 0; u < NF; ++u) {
+            const int b = b0 + u * kBlock;
+            fv[u] = b < a.n_fpartials ? fp[b] : make_double2(0.0, 0.0);
+        }
+#pragma unroll
+        for (int u = 0; u < NF; ++u) {
+            fe[0] += fv[u].x;
+            fe[1] += fv[u].y;
+        }
+    }
+}
+
+// The step pass's extra block where the force pass takes over the finalize
+// (k_pair_step): sums the last force pass's partials before they are
+// overwritten, and copies the parts of the control block that the force pass's
+// blocks read while its finalize block writes it.
+__device__ __forceinline__ void step_snapshot(const FusedArgs &a, double *red, double *out)
+{
+    const int t = threadIdx.x;
+    double fe[2] = {0.0, 0.0};
+    force_partials(a, fe);
+    if (t == 0) {
+        out[SN_EBUILD] = a.ctl->ebuild;
+        out[SN_RUN] = a.ctl->budget != 0 ? 1.0 : 0.0;
+    }
+    const double r = block_fold<2>(fe, red);
+    if (t < 2) out[SN_EPAIR + t] = r;
 }
 
 template <int MODE, bool FC, bool LOOP>
@@ -435,7 +477,12 @@ __global__ __launch_bounds__(kBlock) void k_fused(FusedArgs a)
 {
     extern __shared__ double smem[];
     __shared__ double red[64];
-    fused_tiles<MODE, FC, LOOP>(a, blockIdx.x, gridDim.x, smem, red, a.partials + (size_t)blockIdx.x * kPartRow);
+    double *out = a.partials + (size_t)blockIdx.x * kPartRow;
+    if (MODE == FUSED_STEP && !LOOP && a.step_max && blockIdx.x == gridDim.x - 1) {
+        step_snapshot(a, red, out);
+        return;
+    }
+    fused_tiles<MODE, FC, LOOP>(a, blockIdx.x, gridDim.x, smem, red, out);
 }
 
 // Batched: one item (system, tile) per block; the system's arguments come from
@@ -465,8 +512,10 @@ __global__ __launch_bounds__(kBlock) void k_fused_batch(const FusedArgs *__restr
 // barostat's finalize uses it too.)
 
 // FC: the system uses fixcom (its partials carry the centroid momentum)
-template <bool FC>
-__device__ void finalize_system(const FusedArgs &a, int nblocks, double *red, int *sbuf, int *sflag)
+// SNAP: a block of the force pass does this; the last forces' sums come from the
+// step pass's extra row (step_snapshot), and there are no cells
+template <bool FC, bool SNAP = false>
+__device__ __forceinline__ void finalize_system(const FusedArgs &a, int nblocks, double *red, int *sbuf, int *sflag)
 {
     const int t = threadIdx.x;
     const int P = a.P;
@@ -501,7 +550,7 @@ __device__ void finalize_system(const FusedArgs &a, int nblocks, double *red, in
     // (with a thread to a row, 88 bytes apart, a wave's read touched 44 lines).
     // Loads in fixed batches held in registers, so that a batch's reads are in
     // flight together; out-of-range slots add +0.
-    constexpr int NB = 8, NF = 16, NR = kBlock / kPartRow;
+    constexpr int NB = 8, NR = kBlock / kPartRow;
     const int pq = t & (kPartRow - 1);
     const bool is_max = pq >= PF_EMAX;
     const bool used = pq < PF_COUNT && (FC || pq < PF_PX || pq > PF_PZ);
@@ -519,21 +568,12 @@ __device__ void finalize_system(const FusedArgs &a, int nblocks, double *red, in
     // (summed whether or not this pass needs them, so the loads do not wait
     // for the control block)
     double fe[2] = {0.0, 0.0};   // pair energy, cell virial
-    if (a.pair) {
-        const double2 *fp = reinterpret_cast<const double2 *>(a.fpartials);
-        for (int b0 = t; b0 < a.n_fpartials; b0 += NF * kBlock) {
-            double2 fv[NF];
-#pragma unroll
-            for (int u = 0; u < NF; ++u) {
-                const int b = b0 + u * kBlock;
-                fv[u] = b < a.n_fpartials ? fp[b] : make_double2(0.0, 0.0);
-            }
-#pragma unroll
-            for (int u = 0; u < NF; ++u) {
-                fe[0] += fv[u].x;
-                fe[1] += fv[u].y;
-            }
-        }
+    double snap = 0.0;
+    if constexpr (SNAP) {
+        if (t >= PF_COUNT && t < PF_COUNT + 2)
+            snap = a.partials[(size_t)nblocks * kPartRow + SN_EPAIR + t - PF_COUNT];
+    } else if (a.pair) {
+        force_partials(a, fe);
     }
     // the waves' sums to LDS (slot q of wave w at q NW + w; the force pass's two
     // after the PF_COUNT), then lane q of wave 0 combines the waves' slot q
@@ -567,6 +607,7 @@ __device__ void finalize_system(const FusedArgs &a, int nblocks, double *red, in
             const bool mx = t >= PF_EMAX && t < PF_COUNT;
 #pragma unroll
             for (int u = 1; u < NW; ++u) x = mx ? fmax(x, red[t * NW + u]) : x + red[t * NW + u];
+            if (SNAP && t >= PF_COUNT) x = snap;
         }
         const double emax = sqrt(read_lane(x, PF_EMAX)), dmax = sqrt(read_lane(x, PF_DMAX));
         const double bad = read_lane(x, PF_NONFINITE);
@@ -654,7 +695,7 @@ __device__ void finalize_system(const FusedArgs &a, int nblocks, double *red, in
         }
     }
     // the centroid cell lists of a rebuild (cells recorded by this pass)
-    if (a.lists && a.ncell > 0 && (mode == FUSED_STEP || mode == FUSED_PREP)) {
+    if (!SNAP && a.lists && a.ncell > 0 && (mode == FUSED_STEP || mode == FUSED_PREP)) {
         __syncthreads();
         const bool rb = red[kRedFlag] != 0.0;
         const double rl = red[kRedFlag + 1];
@@ -726,8 +767,9 @@ void launch_fused(const FusedArgs &a, int grid, hipStream_t s)
         launch_boson_pass(a, grid, s);   // Cartesian beads (pimd_boson.hip)
         return;
     }
+    const bool snap = a.mode == FUSED_STEP && a.step_max;   // one block more (step_snapshot)
     auto go = [&](void (*kernel)(FusedArgs)) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), fused_smem_bytes(a.P), s, a);
+        hipLaunchKernelGGL(kernel, dim3(snap ? grid + 1 : grid), dim3(kBlock), fused_smem_bytes(a.P), s, a);
     };
     // a tile per block where the grid covers them
     const bool loop = (a.N + kBlock / a.P - 1) / (kBlock / a.P) > grid;
@@ -783,6 +825,14 @@ __device__ __forceinline__ void unpack_shift(int p, double &sx, double &sy, doub
     sy = (double)(((p >> 10) & 1023) - 512);
     sz = (double)(((p >> 20) & 1023) - 512);
 }
+
+// What a force pass that takes the rebuild decision reads (k_pair_step).
+struct StepDecision {
+    const double *max;    // [n][2] squared excursion and displacement maxima per step-pass block
+    const double *snap;   // SN_*
+    int n;
+    double skin, rc;
+};
 
 // Blocks are dispatched round-robin over the 8 XCDs; map them so that each
 // XCD gets a contiguous range of tiles (neighboring atoms, hence a shared
@@ -928,8 +978,11 @@ __device__ __forceinline__ void bond_forces(const PairArgs &a, int i, int k, dou
 // loop adds 100 us for 677 000 wave-entries of 50 vector instructions (69% of the
 // issue slots; 82 us with the gathers left out, 77 us with the arithmetic left
 // out).  LJ N = 4000, P = 32: 25.4 -> 22.3 us (with the re-tuned S = 2 for 4).
-template <bool BOXDEV = false, bool DIAG = false, bool PAIRED = false>
-__device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, double *s_f)
+// DEC: the rebuild decision is taken here, from the step pass's maxima and
+// snapshot (dec), not read from the control block; there are no cells.
+template <bool BOXDEV = false, bool DIAG = false, bool PAIRED = false, bool DEC = false>
+__device__ __forceinline__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, double *s_f,
+                                          const StepDecision *dec = nullptr)
 {
     const int P = a.P, S = a.S;
     const int G = S * P;                    // lanes per atom
@@ -943,7 +996,20 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
     const double L0 = BOXDEV ? a.ctl->box[0] : a.box[0];
     const double L1 = BOXDEV ? a.ctl->box[1] : a.box[1];
     const double L2 = BOXDEV ? a.ctl->box[2] : a.box[2];
-    int ran = a.ctl->ran, rebuild = a.ctl->rebuild;
+    int ran = 0, rebuild = 0;
+    double rlist = 0.0, mv[2] = {0.0, 0.0};
+    constexpr int ND = kStepDecideBlocks / 64;
+    double2 dm[ND];
+    if constexpr (DEC) {
+#pragma unroll
+        for (int u = 0; u < ND; ++u) {
+            const int b = (t & 63) + u * 64;
+            dm[u] = b < dec->n ? reinterpret_cast<const double2 *>(dec->max)[b] : make_double2(0.0, 0.0);
+        }
+    } else {
+        ran = a.ctl->ran;
+        rebuild = a.ctl->rebuild;
+    }
     const bool listed = act && i < a.n_active;
     const int2 *list = a.nbr + (size_t)(listed ? i : 0) * a.cap;
     const int P3 = 3 * P;
@@ -978,6 +1044,20 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
         }
     };
     read_group();
+    if constexpr (DEC) {
+        // (the expressions of finalize_system)
+#pragma unroll
+        for (int u = 0; u < ND; ++u) {
+            mv[0] = fmax(mv[0], dm[u].x);
+            mv[1] = fmax(mv[1], dm[u].y);
+        }
+        double r[1];
+        wave_fold<2, true>(mv, r);
+        const double emax = sqrt(read_lane(r[0], 0)), dmax = sqrt(read_lane(r[0], 32));
+        ran = dec->snap[SN_RUN] != 0.0;
+        rebuild = dmax + emax > 0.5 * dec->skin + dec->snap[SN_EBUILD];
+        rlist = dec->rc + dec->skin + 2.0 * emax;
+    }
     ran = __builtin_amdgcn_readfirstlane(ran);
     rebuild = __builtin_amdgcn_readfirstlane(rebuild);
     if (!ran) return;          // the system took no step (uniform per block)
@@ -986,7 +1066,7 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
     // need more than kMaxImages periodic images per dim skips the build and
     // flags the state; the image loops below are therefore always bounded.
     constexpr int kMaxImages = 8;
-    const double rl_in = rebuild ? a.ctl->rlist : 0.0;
+    const double rl_in = rebuild ? (DEC ? rlist : a.ctl->rlist) : 0.0;
     const bool rl_ok = isfinite(rl_in) && rl_in > 0.0 && rl_in <= kMaxImages * L0 &&
                        rl_in <= kMaxImages * L1 && rl_in <= kMaxImages * L2;
     if (rebuild && !rl_ok) {
@@ -998,7 +1078,7 @@ __device__ void pair_tile(const PairArgs &a, int tile, int *s_cnt, double *red, 
     // place the hits.  Image shifts come from the integer box indices kept at
     // binning and the wrap of the stencil cell.
     const bool wave_aligned = (G % 64 == 0) || (64 % G == 0);
-    const bool use_cells = rebuild && rl_ok && a.ctl->cell_ok && wave_aligned;
+    const bool use_cells = !DEC && rebuild && rl_ok && a.ctl->cell_ok && wave_aligned;
     // Without cells, in a box of at least twice the list cutoff (no image but
     // the nearest can be in reach): each wave takes every fourth atom of the
     // block and tests all active atoms, 64 at a time in index order, ballots
@@ -1619,6 +1699,35 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
     const int tile = (b < nA) ? xcd_tile(b, nA) : nA + xcd_tile(b - nA, gridDim.x - nA);
     pair_tile<false, false, PAIRED>(a, tile, s_cnt, red, s_f);
 }
+
+// The force pass of a small system, whose block 0 is the step's finalize: the
+// others take the rebuild decision from the step pass's maxima themselves, so
+// that a step is two launches, and the finalize's latency (reads from other
+// XCDs, sums, the control block) runs beside the forces.  Nothing here reads what
+// block 0 writes: the decision's inputs are copied by the step pass
+// (step_snapshot), which also sums the last forces' energies before these
+// overwrite them.  Per step with the finalize as a launch of its own and so: LJ
+// N = 256, P = 8 17.3 -> 15.3 us, N = 1021, P = 7 18.7 -> 17.0, N = 4000, P = 32
+// 40.8 -> 36.2 (500 step-pass blocks: eight 16-byte reads a lane; above, the
+// reads would grow with the square of the system).
+template <bool PAIRED, bool FC>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_pair_step(PairArgs a,
+                                                                                            FusedArgs fa,
+                                                                                            int nblocks)
+{
+    __shared__ int s_cnt[kBlock];
+    __shared__ double red[64];
+    __shared__ double s_f[kBlock * 3];
+    if (blockIdx.x == 0) {
+        finalize_system<FC, true>(fa, nblocks, red, nullptr, nullptr);
+        return;
+    }
+    const StepDecision dec{fa.step_max, fa.partials + (size_t)nblocks * kPartRow, nblocks, fa.skin, fa.rc};
+    const int b = blockIdx.x - 1, nA = a.n_active_tiles;
+    const int tile = (b < nA) ? xcd_tile(b, nA) : nA + xcd_tile(b - nA, gridDim.x - 1 - nA);
+    pair_tile<false, false, PAIRED, true>(a, tile, s_cnt, red, s_f, &dec);
+}
+
 // The same pass with the active tiles on cluster lists (a kernel of its own,
 // so that the per-atom kernel keeps its register budget).
 __global__ __launch_bounds__(kBlock) void k_pair_clusters(PairArgs a)
@@ -1766,6 +1875,17 @@ void launch_pair_npt(const PairArgs &a, int grid, hipStream_t s)
         hipLaunchKernelGGL(k_pair_npt<true>, dim3(grid), dim3(kBlock), 0, s, a);
     else
         hipLaunchKernelGGL(k_pair_npt<false>, dim3(grid), dim3(kBlock), 0, s, a);
+}
+
+void launch_pair_step(const PairArgs &a, const FusedArgs &fa, int fused_blocks, int grid, hipStream_t s)
+{
+    auto go = [&](void (*kernel)(PairArgs, FusedArgs, int)) {
+        hipLaunchKernelGGL(kernel, dim3(grid + 1), dim3(kBlock), 0, s, a, fa, fused_blocks);
+    };
+    if (a.paired)
+        go(fa.fixcom ? k_pair_step<true, true> : k_pair_step<true, false>);
+    else
+        go(fa.fixcom ? k_pair_step<false, true> : k_pair_step<false, false>);
 }
 
 void launch_pair(const PairArgs &a, int grid, hipStream_t s)

@@ -460,6 +460,7 @@ Layout make_layout(const pimd_params *p, int n_active, int n_forced, int cap, do
     // large buffer
     L.stage_both = arr <= kStageBoth;
     L.stage = take(L.stage_both ? 2 * arr : arr);
+    // (cent to cref are cleared, M to nbr_count uploaded, each in one piece)
     L.cent = take(N * 3 * sizeof(double));
     L.cref = take(N * 3 * sizeof(double));
     L.M = take(P * P * sizeof(double));
@@ -805,19 +806,23 @@ int pimd_create(const pimd_params *p, const double *mass, const pimd_topology *t
                 bond_j[(size_t)j * kMaxBonds + deg[j]++] = i >= L.n_forced ? (i | kBondOwned) : i;
             }
     }
-    hipError_t e = hipSuccess;
-    if (e == hipSuccess) e = hipMemcpy(c->d_M, M.data(), M.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->d_MT, MT.data(), MT.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->d_modes, modes.data(), modes.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->d_atoms, atoms.data(), atoms.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->d_mass, m_int.data(), m_int.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->d_orig, c->orig.data(), c->orig.size() * sizeof(int), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->d_inv, inv.data(), inv.size() * sizeof(int), hipMemcpyHostToDevice);
-    if (e == hipSuccess && pair)
-        e = hipMemcpy(c->d_bond_j, bond_j.data(), bond_j.size() * sizeof(int), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(c->d_cref, 0, (size_t)N * 3 * sizeof(double));
-    if (e == hipSuccess) e = hipMemset(c->d_cent, 0, (size_t)N * 3 * sizeof(double));
-    if (e == hipSuccess && pair) e = hipMemset(c->d_nbr_count, 0, (size_t)N * sizeof(int));
+    // The tables lie one after another in the workspace, up to the (zero) list
+    // lengths: one upload, where one for each took 15 us apiece; likewise one
+    // clear of the centroids and the lists' centroids.
+    std::vector<char> image((pair ? L.nbr_count + (size_t)N * sizeof(int) : L.nbr_count) - L.M, 0);
+    auto put = [&](size_t at, const void *src, size_t bytes) {
+        if (bytes) std::memcpy(image.data() + (at - L.M), src, bytes);
+    };
+    put(L.M, M.data(), M.size() * sizeof(double));
+    put(L.MT, MT.data(), MT.size() * sizeof(double));
+    put(L.modes, modes.data(), modes.size() * sizeof(double));
+    put(L.atoms, atoms.data(), atoms.size() * sizeof(double));
+    put(L.mass, m_int.data(), m_int.size() * sizeof(double));
+    put(L.orig, c->orig.data(), c->orig.size() * sizeof(int));
+    put(L.inv, inv.data(), inv.size() * sizeof(int));
+    put(L.bond_j, bond_j.data(), bond_j.size() * sizeof(int));
+    hipError_t e = hipMemcpy(w + L.M, image.data(), image.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemset(w + L.cent, 0, L.M - L.cent);
     if (e == hipSuccess) e = hipMemset(c->d_ctl, 0, sizeof(Ctl));
     if (e == hipSuccess && p->bosonic) {
         // no potential: the force array stays zero, one zero energy partial

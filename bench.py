@@ -63,7 +63,7 @@ KERNEL_SOURCES = ("pimd_device.h", "pimd_fused_mfma.hip", "pimd_internal.h", "pi
 # committed rocprofv3 summaries by (workload, kernel)
 PROFILE_FILES = {
     ("lj", "k_pair"): "k_pair_lj_n4000_p32.txt",
-    ("lj", "k_fused<false>"): "k_fused_lj_n4000_p32.txt",
+    ("lj", "k_fused<0, false, false>"): "k_fused_lj_n4000_p32.txt",
     ("water64", "k_fused_mfma<64, false, false>"): "k_fused_mfma_water_n32766_p64.txt",
     ("water64", "k_pair"): "k_pair_water_n32766_p64.txt",
     ("water64x4", "k_fused_mfma<64, false, false>"): "k_fused_mfma_water_n131070_p64.txt",
@@ -427,10 +427,13 @@ def pair_roofline(workload, spec, x, avgs):
 
 
 def fused_kernel_name(spec, info):
-    # the step passes are instantiated per splitting and fixcom
+    # the step passes are instantiated per splitting and fixcom, the vector-ALU
+    # one per pass (0: the step) and on looping over tiles
     tf = lambda v: "true" if v else "false"
-    return (("k_fused_mfma<%d, %s, %s>" % (spec.n_beads, tf(spec.integrator), tf(spec.fixcom)))
-            if info["transforms"] else "k_fused<%s>" % tf(spec.fixcom))
+    if info["transforms"]:
+        return "k_fused_mfma<%d, %s, %s>" % (spec.n_beads, tf(spec.integrator), tf(spec.fixcom))
+    loop = -(-spec.n_atoms // (256 // spec.n_beads)) > info["fused_blocks"]
+    return "k_fused<0, %s, %s>" % (tf(spec.fixcom), tf(loop))
 
 
 def fused_roofline(workload, spec, info, avgs):

@@ -48,7 +48,7 @@ enum FusedMode : int {
     FUSED_PREP = 3,   // v~ = M v, centroids, excursion; requests a neighbor build
 };
 
-// Device-resident control block.  Written by k_finalize (one block, after
+// Device-resident control block.  Written by the finalize (one block, after
 // each fused pass) and by small host-enqueued kernels; read at kernel start.
 struct Ctl {
     unsigned long long step;   // thermostat step counter s

@@ -10,14 +10,15 @@
 //            (The matrix-core variant is k_fused_mfma, pimd_fused_mfma.hip.)
 // k_pair   : bead-batched short-range forces for all P replicas in one
 //            launch (LJ among active atoms + harmonic bonds), each atom's
-//            neighbor list rebuilt from the centroid cells when requested;
+//            neighbor list rebuilt when requested;
 //            per block, the energy and the cell virial (the pressures of
 //            App. A).  k_pair_npt: the same with the box from the control
 //            block (the barostat's passes are in pimd_npt.hip).
 // k_finalize: one block after the step pass; combines the per-block partials
-//            in block order (deterministic), records estimators and running
+//            in a fixed order (deterministic), records estimators and running
 //            sums, advances the step counter, decides list rebuilds and, at
-//            a rebuild, builds the centroid cell lists.
+//            a rebuild, builds the centroid cell lists.  Small systems' force
+//            pass does this in one of its blocks (k_pair_step).
 #include "pimd_device.h"
 #include "pimd_internal.h"
 
@@ -799,11 +800,11 @@ void launch_finalize(const FusedArgs &a, int fused_blocks, hipStream_t s)
 
 // --------------------------------------------------------------------------
 // Pair forces.  Block = A = kBlock/(S P) atoms, thread (atom, sub-group, bead).
-// When the control block requests it, each atom's lanes first rebuild that
-// atom's list with entries |c_i - c_j + s L| < rlist: from the centroid cells
-// (the 2R+1 cells per dim around the atom's cell, in a fixed order) or, when
-// the box has too few cells, by scanning every active atom's centroid and
-// every periodic image within reach, in (j, image) order.
+// At a rebuild the block first builds its atoms' lists, with entries
+// |c_i - c_j + s L| < rlist: from the centroid cells (the 2R+1 cells per dim
+// around the atom's cell, in a fixed order), or from all listed atoms at their
+// nearest images in index order, or, in a box that holds several images within
+// reach, from all of those, in (j, image) order.
 // --------------------------------------------------------------------------
 __device__ __forceinline__ int pack_shift(int sx, int sy, int sz)
 {

@@ -1309,6 +1309,8 @@ __device__ __forceinline__ void pair_tile(const PairArgs &a, int tile, int *s_cn
     }
 
     if (rebuild) read_group();
+    // (whether the lane's atom has bonds: a lane mask in scalar registers)
+    const unsigned long long bonded = __ballot(act && bond0 >= 0);
     double e = 0.0, wv = 0.0, s12 = 0.0, s6 = 0.0;
     double wd[3] = {0.0, 0.0, 0.0};   // DIAG: sum of fr r_a^2 over the thread's pairs
     int np = 0;
@@ -1432,59 +1434,71 @@ __device__ __forceinline__ void pair_tile(const PairArgs &a, int tile, int *s_cn
         }
         group_sync();                                   // the entries have been read
     }
+    // The lane's place again, from scratch: kept through the loop it took five
+    // registers too many, whose spills wrote 23 MB a launch on the water state
+    // (123.1 -> 122.5 us; 131070 atoms 470 -> 463, the batch's pass 99 -> 96).
+    // Small systems' pass has the registers (DEC; 1% slower with this).
+    int tt = threadIdx.x, P_ = P, G_ = G;
+    if constexpr (!DEC) asm("" : "+v"(tt), "+s"(P_), "+s"(G_));
+    const int la_ = div_small(tt, G_), g_ = tt - la_ * G_, sg_ = div_small(g_, P_), k_ = g_ - sg_ * P_;
+    const int i_ = tile * div_small(kBlock, G_) + la_;
+    const bool own = la_ < A && i_ < a.n_forced && sg_ == 0;   // the lane writes its atom's bead
+    const size_t ib_ = (size_t)i_ * (3 * P_) + k_;
+    const bool bonds = own && ((bonded >> (tt & 63)) & 1) != 0;
     if constexpr (PAIRED) {
         // back to one bead per lane: the sub-group 0 lanes sum the 2S
         // sub-groups' forces of their bead in sub-group order (the staged
         // entries are no longer needed, so their LDS holds the partials: 2S *
         // 3P = 6G doubles of the group's 8G)
-        double *s2 = reinterpret_cast<double *>(ls);
-        if (la < A) {
+        double *s2 = reinterpret_cast<double *>(s_lst + la_ * C);
+        if (la_ < A) {
+            const int u2 = div_small(g_, P_ / 2), kp2 = g_ - u2 * (P_ / 2);
 #pragma unroll
             for (int b2 = 0; b2 < 2; ++b2)
 #pragma unroll
-                for (int d = 0; d < 3; ++d) s2[(sg2 * 3 + d) * P + 2 * kp + b2] = pf[3 * b2 + d];
+                for (int d = 0; d < 3; ++d) s2[(u2 * 3 + d) * P + 2 * kp2 + b2] = pf[3 * b2 + d];
         }
         group_sync();
-        if (act && sg == 0) {
+        if (own) {
             for (int u = 0; u < S2; ++u) {
-                fx += s2[(u * 3 + 0) * P + k];
-                fy += s2[(u * 3 + 1) * P + k];
-                fz += s2[(u * 3 + 2) * P + k];
+                fx += s2[(u * 3 + 0) * P + k_];
+                fy += s2[(u * 3 + 1) * P + k_];
+                fz += s2[(u * 3 + 2) * P + k_];
             }
-            if (bond0 >= 0) {
-                xi = X[ib]; yi = X[ib + P]; zi = X[ib + 2 * P];
+            if (bonds) {
+                xi = X[ib_]; yi = X[ib_ + P]; zi = X[ib_ + 2 * P];
             }
         }
     }
     lj_energy_virial(s12, s6, np, eps4, eps24, ush, e, wv);
 #pragma unroll
     for (int d = 0; d < 3; ++d) wd[d] *= 0.5;   // half of each ordered pair, as the trace
-    if (act && sg == 0 && bond0 >= 0) bond_forces<DIAG>(a, i, k, xi, yi, zi, L0, L1, L2, fx, fy, fz, e, wv, wd);
+    if (bonds) bond_forces<DIAG>(a, i_, k_, xi, yi, zi, L0, L1, L2, fx, fy, fz, e, wv, wd);
     if (!PAIRED && S > 1) {
-        s_f[t * 3] = fx; s_f[t * 3 + 1] = fy; s_f[t * 3 + 2] = fz;
+        s_f[tt * 3] = fx; s_f[tt * 3 + 1] = fy; s_f[tt * 3 + 2] = fz;
         __syncthreads();
-        if (act && sg == 0) {
+        if (own) {
             for (int u = 1; u < S; ++u) {
-                const int o = (la * G + u * P + k) * 3;
+                const int o = (la_ * G + u * P + k_) * 3;
                 fx += s_f[o]; fy += s_f[o + 1]; fz += s_f[o + 2];
             }
         }
     }
-    if (act && sg == 0) {
-        a.f[ib] = fx; a.f[ib + P] = fy; a.f[ib + 2 * P] = fz;
+    if (own) {
+        a.f[ib_] = fx; a.f[ib_ + P] = fy; a.f[ib_ + 2 * P] = fz;
     }
     // block sums (fixed order): energy, then the cell virial after all partials
     if constexpr (DIAG) {
         double e5[5] = {e, wv, wd[0], wd[1], wd[2]};
         const double r = block_fold<5>(e5, red);
-        if (t < 2)
-            a.fpartials[(size_t)tile * 2 + t] = r;
-        else if (t < 5)
-            a.fdiag[(size_t)tile * 3 + t - 2] = r;
+        if (tt < 2)
+            a.fpartials[(size_t)tile * 2 + tt] = r;
+        else if (tt < 5)
+            a.fdiag[(size_t)tile * 3 + tt - 2] = r;
     } else {
         double e1[2] = {e, wv};
         const double r = block_fold<2>(e1, red);
-        if (t < 2) a.fpartials[(size_t)tile * 2 + t] = r;
+        if (tt < 2) a.fpartials[(size_t)tile * 2 + tt] = r;
     }
 }
 

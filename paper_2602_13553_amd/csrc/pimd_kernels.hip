@@ -893,10 +893,12 @@ __device__ __forceinline__ void lj_accumulate(double dx, double dy, double dz, c
     }
 }
 
-// sqrt(x) and 1/sqrt(x) for normal x > 0, from the hardware's estimate (about
-// 2^-24 relative) by two coupled Newton steps and a residual correction of the
-// root (Goldschmidt's iteration); either within an ulp.  A third of the
-// instructions of sqrt and an IEEE division by it.
+// sqrt(x) and its reciprocal, each rounded once: from the hardware's estimate of
+// 1/sqrt(x) by two coupled Newton steps (Goldschmidt's iteration), then a residual
+// correction of the root and one of the reciprocal.  Half the instructions of
+// sqrt and an IEEE division; over 5e7 random x the same to the bit, where no
+// residual leaves the normal range (normal_root).
+__device__ __forceinline__ bool normal_root(double x) { return x > 0x1p-960 && x < 0x1p960; }
 __device__ __forceinline__ double sqrt_rsqrt(double x, double &ir)
 {
     const double y = __builtin_amdgcn_rsq(x);
@@ -908,8 +910,17 @@ __device__ __forceinline__ double sqrt_rsqrt(double x, double &ir)
         h = fma(h, r, h);
     }
     g = fma(fma(-g, g, x), h, g);
-    ir = 2.0 * h;
+    const double i = 2.0 * h;
+    ir = fma(fma(-i, g, 1.0), i, i);
     return g;
+}
+
+// d - L rint(d / L) with iL = 1 / L: the quotient as a division rounds it, so
+// that a distance of half a box goes to the image that the division gives (its
+// product with iL may round to the other one).
+__device__ __forceinline__ double nearest_image(double d, double L, double iL)
+{
+    return d - L * rint(div_by(d, L, iL));
 }
 
 // Harmonic bonds of atom i at bead k (minimum image), added to its force and
@@ -935,14 +946,21 @@ __device__ __forceinline__ void bond_forces(const PairArgs &a, int i, int k, dou
         const int j = jr & ~kBondOwned;
         const size_t jb = (size_t)j * P3 + k;
         double dx = xi - X[jb], dy = yi - X[jb + P], dz = zi - X[jb + 2 * P];
-        dx -= L0 * rint(dx * i0);
-        dy -= L1 * rint(dy * i1);
-        dz -= L2 * rint(dz * i2);
+        dx = nearest_image(dx, L0, i0);
+        dy = nearest_image(dy, L1, i1);
+        dz = nearest_image(dz, L2, i2);
         const double r2 = dx * dx + dy * dy + dz * dz;
-        double ir;
-        const double r = sqrt_rsqrt(r2, ir);
-        const double dr = r - a.bond_r0;
-        const double fr = -2.0 * a.bond_k * dr * ir;
+        double dr, fr;
+        if (normal_root(r2)) {
+            double ir;
+            const double r = sqrt_rsqrt(r2, ir);
+            dr = r - a.bond_r0;
+            fr = div_by(-2.0 * a.bond_k * dr, r, ir);
+        } else {
+            const double r = sqrt(r2);
+            dr = r - a.bond_r0;
+            fr = -2.0 * a.bond_k * dr / r;
+        }
         const double share = owned ? 1.0 : 0.5;   // each bond is seen from both atoms
         e += share * a.bond_k * dr * dr;
         wv += share * fr * r2;

@@ -33,7 +33,8 @@ constexpr size_t kStageBoth = 8u << 20;   // bytes of a state array up to which 
 struct Layout {
     size_t x, yt, v, f, stage, cent, cref, M, MT, modes, atoms, mass, orig, inv, bond_j, nbr_count, nbr,
         partials, step_max, fpartials, ctl, cell_ent, cell_scnt, cinfo, total;
-    int cap, fused_grid, mfma_grid, pair_grid, pair_S, pair_active_tiles, n_active;
+    int fused_grid[kFusedModes];  // vector-ALU blocks of each pass
+    int cap, mfma_grid, pair_grid, pair_S, pair_active_tiles, n_active;
     int n_forced;                 // atoms with lanes in the force pass (bond-owned ones last)
     int valu_tiles, mfma_tiles;
     int ncell, cell_cap, nc[3];   // centroid cells (ncell = 0: none)
@@ -442,7 +443,8 @@ Layout make_layout(const pimd_params *p, int n_active, int n_forced, int cap, do
     const bool pair = is_pair(p->potential);
     L.cap = cap;
     L.n_active = n_active;
-    L.fused_grid = fused_grid(p->n_atoms, p->n_beads);
+    for (int mode = 0; mode < kFusedModes; ++mode)
+        L.fused_grid[mode] = fused_grid(p->n_atoms, p->n_beads, mode, p->fixcom != 0);
     L.mfma_grid = use_mfma(p) ? fused_mfma_grid(p->n_atoms, p->n_beads) : 0;
     L.clusters = pair && use_clusters(p, n_active);
     L.pair_S = pair ? (L.clusters ? 1 : choose_pair_subgroups(p)) : 1;
@@ -476,13 +478,14 @@ Layout make_layout(const pimd_params *p, int n_active, int n_forced, int cap, do
     // partials: per block (single system) or per tile (batched execution)
     L.valu_tiles = (p->n_atoms + (kBlock / p->n_beads) - 1) / (kBlock / p->n_beads);
     L.mfma_tiles = fused_mfma_supported(p->n_beads) ? mfma_block_tiles(p->n_atoms, p->n_beads) : 0;
-    const int nparts = std::max(std::max(L.fused_grid, L.mfma_grid), std::max(L.valu_tiles, L.mfma_tiles));
+    const int nparts = std::max(L.mfma_grid, std::max(L.valu_tiles, L.mfma_tiles));
     L.partials = take((size_t)(nparts + 1) * kPartRow * sizeof(double));
     // The force pass takes over the finalize where the step pass has a tile per
     // block, at most kStepDecideBlocks of them, and lists need no cells.
     L.pair_step = pair && !p->bosonic && !is_npt(p) && !L.clusters && L.ncell == 0 && L.mfma_grid == 0 &&
-                  n_active > 0 && L.fused_grid == L.valu_tiles && L.fused_grid <= kStepDecideBlocks;
-    L.step_max = take(L.pair_step ? (size_t)2 * L.fused_grid * sizeof(double) : 0);
+                  n_active > 0 && L.fused_grid[FUSED_STEP] == L.valu_tiles &&
+                  L.valu_tiles <= kStepDecideBlocks;
+    L.step_max = take(L.pair_step ? (size_t)2 * L.valu_tiles * sizeof(double) : 0);
     L.trap_grid = (p->bosonic && p->potential == PIMD_POT_HARMONIC) ? boson_trap_grid(p->n_atoms, p->n_beads) : 0;
     L.fpartials = take((size_t)2 * std::max(std::max(L.pair_grid, L.trap_grid), 1) * sizeof(double));
     L.ctl = take(sizeof(Ctl));
@@ -602,7 +605,7 @@ void enqueue_fused(pimd_ctx *c, int mode, int kind)
     a.mode = mode;
     // the step pass uses the matrix-core transforms where available
     const bool mfma = (mode == FUSED_STEP) && c->lay.mfma_grid > 0;
-    const int blocks = mfma ? c->lay.mfma_grid : c->lay.fused_grid;
+    const int blocks = mfma ? c->lay.mfma_grid : c->lay.fused_grid[mode];
     size_t e = prof_begin(c, kind);
     if (mfma)
         launch_fused_mfma(a, blocks, c->stream);
@@ -661,8 +664,8 @@ void enqueue_step(pimd_ctx *c)
         FusedArgs a = c->fa;
         a.mode = FUSED_STEP;
         a.step_max = c->d_step_max;
-        launch_fused(a, c->lay.fused_grid, c->stream);
-        launch_pair_step(c->pa, a, c->lay.fused_grid, c->lay.pair_grid, c->stream);
+        launch_fused(a, c->lay.valu_tiles, c->stream);
+        launch_pair_step(c->pa, a, c->lay.valu_tiles, c->lay.pair_grid, c->stream);
         return;
     }
     enqueue_fused(c, FUSED_STEP, PIMD_KERNEL_FUSED);
@@ -1009,8 +1012,8 @@ int pimd_set_state(pimd_ctx *c, const double *x, const double *v, uint64_t step)
     // a barostat's box may differ from params.box (pimd_set_barostat): its
     // first lists come from the all-pairs scan, its cells from later rebuilds
     if (c->lay.npt_grid) a.ncell = 0;
-    launch_fused(a, c->lay.fused_grid, c->stream);
-    launch_finalize(a, c->lay.fused_grid, c->stream);
+    launch_fused(a, c->lay.fused_grid[a.mode], c->stream);
+    launch_finalize(a, c->lay.fused_grid[a.mode], c->stream);
     const bool external = c->p.potential == PIMD_POT_EXTERNAL;
     if (c->lay.npt_grid) {
         launch_pair_npt(c->pa, c->lay.pair_grid, c->stream);
@@ -1021,8 +1024,8 @@ int pimd_set_state(pimd_ctx *c, const double *x, const double *v, uint64_t step)
     if (!external && !c->lay.npt_grid) {
         // external forces: the estimators wait for the caller's forces
         a.mode = FUSED_EST;
-        launch_fused(a, c->lay.fused_grid, c->stream);
-        launch_finalize(a, c->lay.fused_grid, c->stream);
+        launch_fused(a, c->lay.fused_grid[a.mode], c->stream);
+        launch_finalize(a, c->lay.fused_grid[a.mode], c->stream);
     }
     int rc = launch_error(c, "set_state launch");
     if (rc != PIMD_OK) return rc;
@@ -1091,7 +1094,7 @@ int pimd_get_launch_info(const pimd_ctx *c, pimd_launch_info *out)
     if (!c || !out) return fail(nullptr, PIMD_ERR_ARG, "ctx or out is NULL");
     const Layout &L = c->lay;
     out->transforms = L.mfma_grid > 0 ? 1 : 0;
-    out->fused_blocks = L.mfma_grid > 0 ? L.mfma_grid : L.fused_grid;
+    out->fused_blocks = L.mfma_grid > 0 ? L.mfma_grid : L.fused_grid[FUSED_STEP];
     out->pair_subgroups = L.pair_grid > 0 ? L.pair_S : 0;
     out->pair_blocks = L.pair_grid;
     out->cells = L.ncell;

@@ -47,6 +47,7 @@ enum FusedMode : int {
     FUSED_EST = 2,    // estimators of a synchronized state (after set_state)
     FUSED_PREP = 3,   // v~ = M v, centroids, excursion; requests a neighbor build
 };
+constexpr int kFusedModes = 4;
 
 // Device-resident control block.  Written by the finalize (one block, after
 // each fused pass) and by small host-enqueued kernels; read at kernel start.
@@ -269,7 +270,7 @@ int report_error(int code, const char *msg);
 
 // Launchers (pimd_kernels.hip).
 int fused_smem_bytes(int P);
-int fused_grid(int N, int P);
+int fused_grid(int N, int P, int mode, bool fixcom);
 void launch_fused(const FusedArgs &a, int grid, hipStream_t s);
 void launch_finalize(const FusedArgs &a, int fused_blocks, hipStream_t s);
 bool fused_mfma_supported(int P);

@@ -22,6 +22,8 @@
 #include "pimd_device.h"
 #include "pimd_internal.h"
 
+#include <algorithm>
+
 namespace pimd {
 
 // --------------------------------------------------------------------------
@@ -152,15 +154,21 @@ __device__ __forceinline__ void fused_tiles(const FusedArgs &a, int t0, int tstr
             }
         }
         if (spent) return;
-        // The noise of the pass's O steps, formed while those reads are in
-        // flight: it needs the counter alone.  zo: the step's first (or only) O;
-        // zl: OBABO's last O, of the step closed here or of the trap's step.
+        // The noise of the pass's O steps; it needs the counter alone.  zo: the
+        // step's first (or only) O; zl: OBABO's last O, of the step closed here or
+        // of the trap's step.  With a tile per block it is formed while those reads
+        // are in flight; in the loop after the transforms, where a CU's other block
+        // has its reads in flight (ahead of them, with the values held through the
+        // transforms: water N = 131070, P = 64 694 us for 677).
         double zo[3] = {0.0, 0.0, 0.0}, zl[3] = {0.0, 0.0, 0.0};
-        if (a.nvt && act) {
-            if (mode == FUSED_STEP) gauss3(a.seed, oi, (unsigned)k, step, zo, 0u);
-            if (a.obabo && (closing || (ext && mode == FUSED_STEP)))
-                gauss3(a.seed, oi, (unsigned)k, closing ? step - 1 : step, zl, 1u);
-        }
+        auto noise = [&]() {
+            if (a.nvt && act) {
+                if (mode == FUSED_STEP) gauss3(a.seed, oi, (unsigned)k, step, zo, 0u);
+                if (a.obabo && (closing || (ext && mode == FUSED_STEP)))
+                    gauss3(a.seed, oi, (unsigned)k, closing ? step - 1 : step, zl, 1u);
+            }
+        };
+        if (!LOOP) noise();
         __syncthreads();   // the previous tile's (or call's) shared-memory reads are done
         if (!LOOP || tile == t0) {
             if (m_regs) {
@@ -245,6 +253,7 @@ __device__ __forceinline__ void fused_tiles(const FusedArgs &a, int t0, int tstr
 #pragma unroll
                 for (int d = 0; d < 3; ++d) vt[d] -= ucom[d];
             }
+            if (LOOP) noise();
             // absolute mode coordinate x~_k (differs from y~_k only for k = 0)
             const double off = (k == 0) ? sqrtP : 0.0;
             if (ext) {
@@ -730,36 +739,49 @@ __global__ __launch_bounds__(kBlock) void k_finalize_batch(const FusedArgs *tabl
     }
 }
 
-int fused_grid(int N, int P)
+// The pass's kernel: a tile per block, or one that loops over tiles.
+static void (*fused_kernel(int mode, bool fixcom, bool loop))(FusedArgs)
+{
+    // (the passes that end no step leave fixcom's partials, which nothing then
+    // reads, unwritten)
+    if (mode == FUSED_PREP) return k_fused<FUSED_PREP, false, true>;
+    if (mode == FUSED_EST) return k_fused<FUSED_EST, false, true>;
+    if (mode == FUSED_CLOSE && fixcom)
+        return loop ? k_fused<FUSED_CLOSE, true, true> : k_fused<FUSED_CLOSE, true, false>;
+    if (mode == FUSED_CLOSE) return loop ? k_fused<FUSED_CLOSE, false, true> : k_fused<FUSED_CLOSE, false, false>;
+    if (fixcom) return loop ? k_fused<FUSED_STEP, true, true> : k_fused<FUSED_STEP, true, false>;
+    return loop ? k_fused<FUSED_STEP, false, true> : k_fused<FUSED_STEP, false, false>;
+}
+
+// Blocks of a pass: a tile per block while all are resident at once, else as
+// many as are resident of the kernel that loops.  Each by its own registers: the
+// looping step kernel keeps the noise's constants across tiles (229 VGPRs, two
+// waves per SIMD; one tile takes 115, four).  Sized by the one-tile kernel, whose
+// blocks twice outnumber those that fit, the loop ran in two rounds and staged
+// the matrix twice: the trap's step at N = 40000, P = 8 took 26.3 us, now
+// 20.0; at N = 33000, P = 24 48.3 and 41.1; water N = 131070, P = 64 724 and 677.
+int fused_grid(int N, int P, int mode, bool fixcom)
 {
     const int A = kBlock / P;
     const int ntiles = (N + A - 1) / A;
     int dev = 0, ncu = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        hipDeviceProp_t prop;
-        if (hipGetDeviceProperties(&prop, dev) == hipSuccess) ncu = prop.multiProcessorCount;
-    }
-    // large P needs more than the default 64 KB of dynamic LDS per block
-    auto allow = [&](const void *kernel) {
-        if (fused_smem_bytes(P) <= 64 * 1024) return;
-        (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, fused_smem_bytes(P));
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        ncu = 256;
+    auto resident = [&](bool loop) {
+        const auto kernel = fused_kernel(mode, fixcom, loop);
+        // large P needs more than the default 64 KB of dynamic LDS per block
+        if (fused_smem_bytes(P) > 64 * 1024)
+            (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      fused_smem_bytes(kMaxBeads));
+        int per_cu = 1;
+        if (ntiles <= ncu) return ncu;   // (one block per CU always is)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, fused_smem_bytes(P)) !=
+                hipSuccess || per_cu < 1)
+            per_cu = 1;
+        return ncu * per_cu;
     };
-    allow((const void *)k_fused<FUSED_PREP, false, true>);
-    allow((const void *)k_fused<FUSED_EST, false, true>);
-    allow((const void *)k_fused<FUSED_STEP, false, false>);
-    allow((const void *)k_fused<FUSED_STEP, false, true>);
-    allow((const void *)k_fused<FUSED_STEP, true, false>);
-    allow((const void *)k_fused<FUSED_STEP, true, true>);
-    allow((const void *)k_fused<FUSED_CLOSE, false, false>);
-    allow((const void *)k_fused<FUSED_CLOSE, false, true>);
-    allow((const void *)k_fused<FUSED_CLOSE, true, false>);
-    allow((const void *)k_fused<FUSED_CLOSE, true, true>);
-    int per_cu = 1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_fused<FUSED_STEP, false, false>, kBlock, fused_smem_bytes(P)) !=
-            hipSuccess || per_cu < 1)
-        per_cu = 1;
-    const int cap = ncu * per_cu;
-    return ntiles < cap ? ntiles : cap;
+    return ntiles <= resident(false) ? ntiles : std::min(ntiles, resident(true));
 }
 
 void launch_fused(const FusedArgs &a, int grid, hipStream_t s)
@@ -769,25 +791,9 @@ void launch_fused(const FusedArgs &a, int grid, hipStream_t s)
         return;
     }
     const bool snap = a.mode == FUSED_STEP && a.step_max;   // one block more (step_snapshot)
-    auto go = [&](void (*kernel)(FusedArgs)) {
-        hipLaunchKernelGGL(kernel, dim3(snap ? grid + 1 : grid), dim3(kBlock), fused_smem_bytes(a.P), s, a);
-    };
-    // a tile per block where the grid covers them
     const bool loop = (a.N + kBlock / a.P - 1) / (kBlock / a.P) > grid;
-    // (the passes that end no step leave fixcom's partials, which nothing then
-    // reads, unwritten)
-    if (a.mode == FUSED_PREP)
-        go(k_fused<FUSED_PREP, false, true>);
-    else if (a.mode == FUSED_EST)
-        go(k_fused<FUSED_EST, false, true>);
-    else if (a.mode == FUSED_CLOSE && a.fixcom)
-        go(loop ? k_fused<FUSED_CLOSE, true, true> : k_fused<FUSED_CLOSE, true, false>);
-    else if (a.mode == FUSED_CLOSE)
-        go(loop ? k_fused<FUSED_CLOSE, false, true> : k_fused<FUSED_CLOSE, false, false>);
-    else if (a.fixcom)
-        go(loop ? k_fused<FUSED_STEP, true, true> : k_fused<FUSED_STEP, true, false>);
-    else
-        go(loop ? k_fused<FUSED_STEP, false, true> : k_fused<FUSED_STEP, false, false>);
+    hipLaunchKernelGGL(fused_kernel(a.mode, a.fixcom != 0, loop), dim3(snap ? grid + 1 : grid), dim3(kBlock),
+                       fused_smem_bytes(a.P), s, a);
 }
 
 void launch_finalize(const FusedArgs &a, int fused_blocks, hipStream_t s)

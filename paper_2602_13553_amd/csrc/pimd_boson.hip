@@ -797,8 +797,9 @@ struct WeightLds {
 // by a rounding or two: LJ bosons N = 500, P = 32, whose rings hardly exchange,
 // had link probabilities off by 8e-15, now by 7e-91; the trap N = 500, P = 32 by
 // 4.7e-15, now 1.3e-15; 1.9e-15 and 1.5e-15 where exchange is strong, N = 512.
-// Largest error, root mean square over 24 states, against 113-bit sums.)  A call that the solve left
-// runs the recursion in log space here instead (block 0).
+// Largest error, root mean square over 24 states, against 113-bit sums.)
+// A call that the solve left runs the recursion in log space here instead
+// (block 0).
 __global__ __launch_bounds__(kBlock) void k_boson_weights(BosonArgs a)
 {
     __shared__ union { WeightLds v; SeqLds q; } lds;

@@ -23,6 +23,7 @@
 #include "pimd_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace pimd {
 
@@ -560,21 +561,31 @@ __device__ __forceinline__ void finalize_system(const FusedArgs &a, int nblocks,
     // (with a thread to a row, 88 bytes apart, a wave's read touched 44 lines).
     // Loads in fixed batches held in registers, so that a batch's reads are in
     // flight together; out-of-range slots add +0.
-    constexpr int NB = 8, NR = kBlock / kPartRow;
+    // Eight reads of a thread at a time up to 128 rows, 32 above, so that the rows of
+    // a card full of blocks (1024) take two batches: eight took 9.9 us where 512
+    // rows took 7.
+    constexpr int NR = kBlock / kPartRow;
     const int pq = t & (kPartRow - 1);
     const bool is_max = pq >= PF_EMAX;
     const bool used = pq < PF_COUNT && (FC || pq < PF_PX || pq > PF_PZ);
     double part = 0.0;
-    for (int b0 = t / kPartRow; b0 < nblocks; b0 += NB * NR) {
-        double pv[NB];
+    auto rows = [&](auto nb) {
+        constexpr int NB = decltype(nb)::value;
+        for (int b0 = t / kPartRow; b0 < nblocks; b0 += NB * NR) {
+            double pv[NB];
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int b = b0 + u * NR;
-            pv[u] = (used && b < nblocks) ? a.partials[(size_t)b * kPartRow + pq] : 0.0;
+            for (int u = 0; u < NB; ++u) {
+                const int b = b0 + u * NR;
+                pv[u] = (used && b < nblocks) ? a.partials[(size_t)b * kPartRow + pq] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u) part = is_max ? fmax(part, pv[u]) : part + pv[u];
         }
-#pragma unroll
-        for (int u = 0; u < NB; ++u) part = is_max ? fmax(part, pv[u]) : part + pv[u];
-    }
+    };
+    if (SNAP || nblocks <= 8 * NR)
+        rows(std::integral_constant<int, 8>());
+    else
+        rows(std::integral_constant<int, 32>());
     // (summed whether or not this pass needs them, so the loads do not wait
     // for the control block)
     double fe[2] = {0.0, 0.0};   // pair energy, cell virial

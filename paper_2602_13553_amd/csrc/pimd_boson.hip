@@ -43,7 +43,8 @@
 //                   the remaining link forces
 // Links beyond kWideLink (in units of 1/beta_n), where the exponents would
 // leave 32 bits, and non-finite ones send the call through the recursion in
-// log space (seq_recursion: one block of k_boson_weights, sequential in n).
+// log space (seq_recursion: one block of k_boson_weights, sequential in n); so
+// do up to kBosonFew particles, without the solve's and the adjoint's launches.
 #include "../../include/pimd.h"
 #include "pimd_internal.h"
 #include "pimd_device.h"
@@ -431,6 +432,7 @@ __global__ __launch_bounds__(kBlock) void k_boson_prep(BosonArgs a)
     const BosonScr scr(a);
     const int tiles = boson_tiles(N), inner = inner_blocks(N, P);
     if ((int)blockIdx.x < tiles) {
+        if (N <= kBosonFew) return;
         const int tile = blockIdx.x;
         int b = (int)((sqrtf(8.0f * (float)tile + 1.0f) - 1.0f) * 0.5f);
         while (boson_tile(b + 1, 0) <= tile) ++b;
@@ -818,7 +820,7 @@ __global__ __launch_bounds__(kBlock) void k_boson_weights(BosonArgs a)
     Quad g[NQ];
 #pragma unroll
     for (int u = 0; u < NQ; ++u) g[u] = quad_at(wt, ge, (t >> 6) + u * (kBlock / 64), r);
-    if (scr.slow[0]) {
+    if (N <= kBosonFew || scr.slow[0]) {
         if (tile == 0) seq_recursion(a, lds.q);
         return;
     }
@@ -1453,9 +1455,10 @@ void launch_boson_springs(const BosonArgs &a, hipStream_t st)
 {
     const int tiles = boson_tiles(a.N), inner = inner_blocks(a.N, a.P);
     hipLaunchKernelGGL(k_boson_prep, dim3(tiles + inner + 1), dim3(kBlock), 0, st, a);
-    hipLaunchKernelGGL(k_boson_solve, dim3(1), dim3(kSolve), 0, st, a);
+    const bool few = a.N <= kBosonFew;   // k_boson_weights runs the whole recursion
+    if (!few) hipLaunchKernelGGL(k_boson_solve, dim3(1), dim3(kSolve), 0, st, a);
     hipLaunchKernelGGL(k_boson_weights, dim3(tiles), dim3(kBlock), 0, st, a);
-    hipLaunchKernelGGL(k_boson_adjoint, dim3(1), dim3(kSolve), 0, st, a);
+    if (!few) hipLaunchKernelGGL(k_boson_adjoint, dim3(1), dim3(kSolve), 0, st, a);
     hipLaunchKernelGGL(k_boson_rows, dim3((a.N + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0,
                        st, a);
     hipLaunchKernelGGL(k_boson_cols, dim3((a.N + kColLanes - 2) / (kColLanes - 1)), dim3(kColBlock), 0,

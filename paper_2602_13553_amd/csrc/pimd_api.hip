@@ -28,7 +28,12 @@ constexpr int kGraphChunk = 32;   // steps per captured graph
 // cell build: LJ N = 1021, P = 7 45 + 8 us with cells, 13 without; N = 4000,
 // P = 32 46 + 22 against 42; 10922 listed atoms at P = 64 242 + 75 against 360.
 constexpr int kScanAtoms = 4096;
-constexpr size_t kStageBoth = 8u << 20;   // bytes of a state array up to which staging holds two
+// Bytes of a state array up to which the staging buffer holds two (get_state then
+// converts positions and momenta ahead of the copies, which saves 11 to 16 us at
+// any size: 66 us to 55 at 48 KB, 156 to 144 at 1 MB, 769 to 750 at 6 MB).  The
+// second one counts in pimd_workspace_bytes, by which callers admit systems: at
+// most 1 MB a context.
+constexpr size_t kStageBoth = 1u << 20;
 
 struct Layout {
     size_t x, yt, v, f, stage, cent, cref, M, MT, modes, atoms, mass, orig, inv, bond_j, nbr_count, nbr,
@@ -458,8 +463,6 @@ Layout make_layout(const pimd_params *p, int n_active, int n_forced, int cap, do
     L.yt = take(arr);
     L.v = take(arr);
     L.f = take(forces_in_array(p) ? arr : 0);
-    // get_state converts positions and momenta together where that doubles no
-    // large buffer
     L.stage_both = arr <= kStageBoth;
     L.stage = take(L.stage_both ? 2 * arr : arr);
     // (cent to cref are cleared, M to nbr_count uploaded, each in one piece)

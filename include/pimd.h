@@ -357,7 +357,9 @@ int pimd_set_barostat(pimd_ctx *ctx, const double *box, const double *vw);
  * receives the spring forces -dV_B/dx; prob ([N][N], device, or NULL) the
  * probability that bead P-1 of particle l links to bead 0 of particle l'.
  * Work is enqueued on stream (a hipStream_t; NULL = the null stream); the
- * call allocates its scratch (about 9 N^2 bytes), waits for the stream and
+ * call allocates its scratch (64 KB for each 64 x 64 tile of the triangle, T
+ * (T + 1) / 2 of them for T = N / 64 rounded up, and 8 KB and more of vectors:
+ * 70 KB up to N = 64, 0.2 MB at 128, 9.1 MB at 1024), waits for the stream and
  * frees it before it returns.
  * Errors: ARG (NULL x, f or out, N < 1, P < 1, kspring < 0 or not finite,
  * beta_n <= 0, a negative or non-finite box length), UNSUPPORTED (N > 1024,

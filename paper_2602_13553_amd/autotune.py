@@ -21,8 +21,11 @@ stream over the same steps:
 
 From the timings it picks three things:
 
-* per P, the smallest N*P from which the matrix cores are at least as fast
-  at every larger size of the sweep;
+* per P, the smallest N*P from which the matrix cores are at most 2% slower
+  at every larger size of the sweep (the pass alone, with the finalize as a
+  launch of its own as in all profiled steps; up to 512 blocks the vector-ALU
+  step also merges the finalize into the force pass, which of the sizes above
+  the thresholds concerns N = 2048 at P = 64 alone);
 * per (P, N), the fewest sub-groups S within 2% of the fastest, once for
   LJ and once for the water-shaped system.
 
@@ -170,8 +173,8 @@ def header_text(result: dict, mfma_min: list, table: list, water: list) -> str:
         "#pragma once\n\n"
         "namespace pimd {\n"
         "namespace tuning {\n\n"
-        "// Smallest N*P from which the matrix-core step pass is faster than the\n"
-        "// vector-ALU one, for P = 16, 32, 64.\n"
+        "// Smallest N*P from which the matrix-core step pass is at most 2%% slower\n"
+        "// than the vector-ALU one at every size of the sweep, for P = 16, 32, 64.\n"
         "constexpr long long kMfmaMinBeadAtoms[3] = {%s};\n\n"
         "// Force-pass lane sub-groups per atom for P = 8, 16, 32, 64 (rows) and N in\n"
         "// [2^6, 2^7), [2^7, 2^8), ..., [2^15, 2^16) (columns; clamped at both ends),\n"

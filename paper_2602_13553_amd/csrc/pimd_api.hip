@@ -27,6 +27,9 @@ constexpr int kGraphChunk = 32;   // steps per captured graph
 // before it costs more than the cells save.  A rebuilding step's force pass and
 // cell build: LJ N = 1021, P = 7 45 + 8 us with cells, 13 without; N = 4000,
 // P = 32 46 + 22 against 42; 10922 listed atoms at P = 64 242 + 75 against 360.
+// The two cross near 9000 atoms (whole steps at P = 8: N = 8000 33.0 us with
+// cells, 28.0 without; N = 10000 with a rebuild every other step 83 and 97), so
+// the line is on the safe side of it, at the largest size first measured.
 constexpr int kScanAtoms = 4096;
 // Bytes of a state array up to which the staging buffer holds two (get_state then
 // converts positions and momenta ahead of the copies, which saves 11 to 16 us at
@@ -393,7 +396,10 @@ void cell_grid(const pimd_params *p, int n_active, double e_guess, Layout &L)
 }
 
 // Transform variant of the step pass: the flags, else the tuned size at which
-// the matrix cores overtake the vector ALUs for this P.
+// the matrix cores overtake the vector ALUs for this P.  (Whole steps of LJ
+// liquids on both sides, vector ALUs and matrix cores: P = 16 N = 8192 43.6 and
+// 46.9 us, 16384 69.7 and 68.6; P = 32 4096 37.8 and 43.0, 8192 67.1 and 64.5; P =
+// 64 1024 28.5 and 35.1, 2048 40.4 and 41.1, 3000 64.4 and 57.4.)
 bool use_mfma(const pimd_params *p)
 {
     const int P = p->n_beads;

@@ -1013,7 +1013,8 @@ __device__ __forceinline__ void bond_forces(const PairArgs &a, int i, int k, dou
 // latency phases and about 130 vector instructions per wave are what is left; the
 // loop adds 100 us for 677 000 wave-entries of 50 vector instructions (69% of the
 // issue slots; 82 us with the gathers left out, 77 us with the arithmetic left
-// out).  LJ N = 4000, P = 32: 25.4 -> 22.3 us (with the re-tuned S = 2 for 4).
+// out).  LJ N = 4000, P = 32: 24.5 -> 19.9 us a launch in the kernel trace (with
+// the re-tuned S = 2 for 4, and the block's sums by lane swaps).
 // DEC: the rebuild decision is taken here, from the step pass's maxima and
 // snapshot (dec), not read from the control block; there are no cells.
 template <bool BOXDEV = false, bool DIAG = false, bool PAIRED = false, bool DEC = false>

@@ -968,7 +968,7 @@ __device__ __forceinline__ void bond_forces(const PairArgs &a, int i, int k, dou
         dz = nearest_image(dz, L2, i2);
         const double r2 = dx * dx + dy * dy + dz * dz;
         double dr, fr;
-        if (normal_root(r2)) {
+        if (__builtin_expect(normal_root(r2), 1)) {
             double ir;
             const double r = sqrt_rsqrt(r2, ir);
             dr = r - a.bond_r0;

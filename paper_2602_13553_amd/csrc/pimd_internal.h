@@ -236,10 +236,10 @@ constexpr int kBosonMaxN = 1024;   // particles (the sequential kernels' LDS)
 constexpr int kBosonTile = 64;     // tile side: the lanes of a wave
 // Particles up to which the recursion runs in log space, row by row: two launches
 // fewer than the blocked solve, whose chain takes 64 steps for any number.  A
-// trap's step at P = 4 takes 28.7 us so and 35.8 by the solve for 2 particles,
-// 33.9 and 37.4 for 5, 38.6 and 38.2 for 7 (one exchange call 41.4 and 49.4, 49.4
-// and 51.9, 53.7 and 52.3).
-constexpr int kBosonFew = 5;
+// trap's step at P = 4 takes 27.3 us so and 36.3 by the solve for 2 particles,
+// 37.5 and 38.1 for 6, 39.2 and 38.5 for 7 (one exchange call 43.2 and 52.3, 51.2
+// and 52.4, 53.1 and 52.4).
+constexpr int kBosonFew = 6;
 constexpr int kBosonInnerMax = 256;   // blocks (and partial energies) of the inner springs
 constexpr __host__ __device__ inline int boson_blocks(int N) { return (N + kBosonTile - 1) / kBosonTile; }
 constexpr __host__ __device__ inline int boson_tile(int b, int cb) { return b * (b + 1) / 2 + cb; }
